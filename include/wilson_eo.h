@@ -362,7 +362,8 @@ typedef struct {
 } weo_sap_params;
 
 /* Bytes of device workspace wilson_eo_sap needs (three sets of nrhs full
- * fields: carried residual and the two colours' last block solutions). */
+ * fields: carried residual, solution so far and block faces, or the two
+ * colours' last block solutions). */
 size_t wilson_eo_sap_workspace_bytes(const weo_lattice* lat, const weo_format* fmt, int nrhs);
 
 /* psi = K eta for nrhs full fields (each the packed even half followed by the

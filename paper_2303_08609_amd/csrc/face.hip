@@ -25,6 +25,7 @@
 // compaction itself runs along x: the slice x = 0 holds the sites of one
 // parity in only every other (y, z, t) row, so f = (y + Ly (z + Lz t)) / 2
 // (the rows are compacted along y), which again pairs the two sides' sites.
+#include "half_spinor.h"
 #include "hop_core.h"
 
 namespace weo {
@@ -68,64 +69,6 @@ __device__ __forceinline__ uint32_t face_site(const Geom& g, uint32_t f, int sid
     }
 }
 
-// Spin projection with (1 - S gamma_mu) to a half spinor (the rules of hop_dir).
-template <int MU, int S, class C>
-__device__ __forceinline__ void face_project(const C* p, C* h) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const C p0 = p[c], p1 = p[3 + c], p2 = p[6 + c], p3 = p[9 + c];
-        C h0, h1;
-        if constexpr (MU == 0) {
-            h0 = S > 0 ? add(p0, imul(p3)) : sub(p0, imul(p3));
-            h1 = S > 0 ? add(p1, imul(p2)) : sub(p1, imul(p2));
-        } else if constexpr (MU == 1) {
-            h0 = S > 0 ? add(p0, p3) : sub(p0, p3);
-            h1 = S > 0 ? sub(p1, p2) : add(p1, p2);
-        } else if constexpr (MU == 2) {
-            h0 = S > 0 ? add(p0, imul(p2)) : sub(p0, imul(p2));
-            h1 = S > 0 ? sub(p1, imul(p3)) : add(p1, imul(p3));
-        } else {
-            h0 = S > 0 ? p2 : p0;
-            h1 = S > 0 ? p3 : p1;
-        }
-        h[c] = h0;
-        h[3 + c] = h1;
-    }
-}
-
-// acc += a * (the full spinor of (1 - S gamma_mu) rebuilt from half spinor g)
-template <int MU, int S, class C, class R>
-__device__ __forceinline__ void face_rebuild(const C* g, R a, C* acc) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const C g0 = g[c], g1 = g[3 + c];
-        C u0 = g0, u1 = g1, l0, l1;         // upper rows; lower rows
-        if constexpr (MU == 0) {
-            l0 = S > 0 ? scal(R(-1), imul(g1)) : imul(g1);
-            l1 = S > 0 ? scal(R(-1), imul(g0)) : imul(g0);
-        } else if constexpr (MU == 1) {
-            l0 = S > 0 ? scal(R(-1), g1) : g1;
-            l1 = S > 0 ? g0 : scal(R(-1), g0);
-        } else if constexpr (MU == 2) {
-            l0 = S > 0 ? scal(R(-1), imul(g0)) : imul(g0);
-            l1 = S > 0 ? imul(g1) : scal(R(-1), imul(g1));
-        }
-        if constexpr (MU == 3) {
-            // (1 - S gamma_t) = 2 x the projector on rows 2, 3 (S > 0) or 0, 1
-            const int o = S > 0 ? 6 : 0;
-            acc[o + c].x = fma(R(2) * a, g0.x, acc[o + c].x);
-            acc[o + c].y = fma(R(2) * a, g0.y, acc[o + c].y);
-            acc[o + 3 + c].x = fma(R(2) * a, g1.x, acc[o + 3 + c].x);
-            acc[o + 3 + c].y = fma(R(2) * a, g1.y, acc[o + 3 + c].y);
-        } else {
-            acc[c].x = fma(a, u0.x, acc[c].x);         acc[c].y = fma(a, u0.y, acc[c].y);
-            acc[3 + c].x = fma(a, u1.x, acc[3 + c].x); acc[3 + c].y = fma(a, u1.y, acc[3 + c].y);
-            acc[6 + c].x = fma(a, l0.x, acc[6 + c].x); acc[6 + c].y = fma(a, l0.y, acc[6 + c].y);
-            acc[9 + c].x = fma(a, l1.x, acc[9 + c].x); acc[9 + c].y = fma(a, l1.y, acc[9 + c].y);
-        }
-    }
-}
-
 template <int SP, int LP, bool L12, bool DAG, int MU>
 __global__ void __launch_bounds__(64) k_face_pack(const FaceParams P) {
     using R = typename Arith<SP>::R;
@@ -140,7 +83,7 @@ __global__ void __launch_bounds__(64) k_face_pack(const FaceParams P) {
     if (blockIdx.z == 0) {
         // slice x_mu = 0: the forward term (projector 1 - SF gamma_mu) of the block below
         load_rec<SP, 12>(in, P.g.vh, face_site<MU>(P.g, f, 0, q), p);
-        face_project<MU, SF>(p, h);
+        half_project<MU, SF>(p, h);
         store_rec<SP, 6>(P.lo + (size_t)rhs * P.face_bytes, P.nf, f, h);
     } else {
         // slice x_mu = L-1: the backward term (projector 1 + SF gamma_mu, U^dag)
@@ -149,16 +92,8 @@ __global__ void __launch_bounds__(64) k_face_pack(const FaceParams P) {
         load_rec<SP, 12>(in, P.g.vh, ih, p);
         C u[9], w[6];
         load_link_as<LP, L12, false>(P.u + (size_t)(2 * MU + q) * P.link_block, P.g.vh, ih, u);
-        face_project<MU, -SF>(p, w);
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                C g = mulc(u[a], w[3 * s]);
-                g = fmac_(u[3 + a], w[3 * s + 1], g);
-                g = fmac_(u[6 + a], w[3 * s + 2], g);
-                h[3 * s + a] = g;
-            }
+        half_project<MU, -SF>(p, w);
+        half_su3<false>(u, w, h);
         store_rec<SP, 6>(P.hi + (size_t)rhs * P.face_bytes, P.nf, f, h);
     }
 }
@@ -182,7 +117,7 @@ __global__ void __launch_bounds__(64) k_face_unpack(const FaceParams P) {
         const C ph = mk<C>((R)P.ph_lo[0], -(R)P.ph_lo[1]);
 #pragma unroll
         for (int k = 0; k < 6; ++k) g[k] = mul(ph, h[k]);
-        face_rebuild<MU, -SF>(g, a, acc);
+        half_rebuild<MU, -SF>(g, a, acc);
         store_rec<SP, 12>(out, P.g.vh, ih, acc);
     } else {
         // output slice x_mu = L-1: forward term from the block above, times U_mu(x)
@@ -194,16 +129,8 @@ __global__ void __launch_bounds__(64) k_face_unpack(const FaceParams P) {
         const C ph = mk<C>((R)P.ph_hi[0], (R)P.ph_hi[1]);
 #pragma unroll
         for (int k = 0; k < 6; ++k) h[k] = mul(ph, h[k]);
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                C t = mul(u[3 * b], h[3 * s]);
-                t = fma_(u[3 * b + 1], h[3 * s + 1], t);
-                t = fma_(u[3 * b + 2], h[3 * s + 2], t);
-                g[3 * s + b] = t;
-            }
-        face_rebuild<MU, SF>(g, a, acc);
+        half_su3<true>(u, h, g);
+        half_rebuild<MU, SF>(g, a, acc);
         store_rec<SP, 12>(out, P.g.vh, ih, acc);
     }
 }

@@ -20,9 +20,12 @@
 //
 // One workgroup per block (lane = site, at most 256 sites), so a block's
 // whole solve runs out of LDS and registers: the block residual is shared
-// through LDS for the in-block hops, the block sums of MR reduce through
-// wavefront shuffles and LDS, and the fields are read and written once per
-// sweep.  The workgroups of the other colour exit at once.
+// through LDS for the in-block hops, the block sums of MR reduce within the
+// wavefronts and through LDS, and the fields are read and written once per
+// sweep.  Two kernels: k_sap_block, and k_sap_sweep for the block shapes
+// whose faces do not fit the scratch fields (in it the workgroups of the
+// other colour exit at once).
+#include "half_spinor.h"
 #include "hop_core.h"
 #include "weo_internal.h"
 
@@ -211,6 +214,403 @@ __global__ void __launch_bounds__(kSapMaxSites) k_sap_sweep(const SapParams P) {
 #pragma unroll
     for (int k = 0; k < 12; ++k) ph[k] = add(ph[k], e[k]);
     store_rec<SP, 12>(P.phi + po, n, st.ih, ph);
+}
+
+// ---- the block sweep with projected faces ----------------------------------------
+// k_sap_block: the same sweep with everything between sweeps kept in block
+// order.  A block's own 4 links per site stay in registers for the whole
+// sweep: the forward hop of direction mu multiplies the neighbour's projected
+// residual by U_mu(x), and the backward hop is multiplied at its source, which
+// owns that link, and handed over through LDS as a half spinor.  The coupling
+// between blocks is exchanged the same way: a block writes only the projected
+// half spinors of its faces (the upper ones already times U^dag), so the
+// receiver reads no full increments and no foreign links.  Residual, solution
+// and faces are [block][plane][site of the block] in the workspace: a
+// wavefront reads consecutive 16-byte words, where the lattice order gives a
+// 4^4 block pieces of 32 bytes.  The source is read and the solution written
+// in lattice order in the first and last cycle only.  Only one colour's
+// blocks are launched, x neighbours on one XCD (they share cache lines of the
+// links).
+// What bounds it: vector issue (about 1300 instructions per lane and step,
+// 200 of them the FP64 block sums) at 2 wavefronts per SIMD -- 256 registers
+// and 74 KiB of LDS for 256 sites.  One sweep at 32^3x64 with 4^4 blocks and
+// 4 steps: 290 us, against 1390 us for k_sap_sweep, whose 8 links per site
+// and solution cost half the occupancy and whose neighbour reads fetch whole
+// cache lines for 32 bytes.
+struct SapBlockParams {
+    Geom g;
+    int b[4], nb[4];        // block extents; blocks per direction
+    int cb[4];              // blocks of one colour per direction (nb, halved along the first split direction)
+    FastDiv d_b[4];         // division by b
+    int split;              // that direction; -1 when one block spans the lattice
+    int bvol;
+    int colour;
+    int nmr;
+    float kappa;
+    float ph[4][2];
+    int wrap[4];            // a block spans mu and the phase there is not 1
+    int foff[4];            // 16-byte words of a block's faces before direction mu
+    int fwords;             // 16-byte words of one block's faces
+    const uint8_t* u;
+    size_t link_block;
+    size_t half_bytes;      // one parity of one field
+    size_t field_words;     // 16-byte words of one field in block order
+    size_t face_words;      // 16-byte words of the faces of one colour's blocks, one rhs
+    const uint8_t* eta;     // residual in lattice order (first cycle) or null
+    uint4* rho;             // residual in block order: read when eta is null
+    int rho_out;            // write it back
+    const uint4* fin;       // faces of the other colour's last sweep or null
+    uint4* fout;            // faces of this sweep or null
+    const uint4* pin;       // solution so far in block order, or null
+    const uint8_t* pin_lat; // ... or in lattice order, or null (both null: zero)
+    uint4* pout;            // solution in block order, or null:
+    uint8_t* pout_lat;      // ... in lattice order
+};
+
+__device__ __forceinline__ void sap_load12(const uint4* p, uint32_t stride, float2* v) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) St<P_F32>::unpack16(p[k * stride], v + 2 * k);
+}
+__device__ __forceinline__ void sap_store12(uint4* p, uint32_t stride, const float2* v) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) p[k * stride] = St<P_F32>::pack16(v + 2 * k);
+}
+
+// Sum over the wavefront, valid in lane 63: DPP moves within the rows of 16
+// lanes and broadcasts between them, where __shfl_xor takes six round trips
+// through the LDS hardware.
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+    v = dpp_add<0xb1, 0xf>(v);      // quad_perm 1,0,3,2
+    v = dpp_add<0x4e, 0xf>(v);      // quad_perm 2,3,0,1
+    v = dpp_add<0x141, 0xf>(v);     // row_half_mirror: the other quad of 8
+    v = dpp_add<0x140, 0xf>(v);     // row_mirror: the other half of 16
+    v = dpp_add<0x142, 0xa>(v);     // row_bcast15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(v);  // row_bcast31 into rows 2 and 3
+}
+
+// NT lanes per workgroup (bvol <= NT); slot NT of every LDS row is zero and
+// stands for the neighbour of a hop that leaves the block.
+template <int NT> struct SapBlockLds {
+    float2 res[12][NT + 1];
+    float2 bw[4][6][NT + 1];
+    double red[NT / 64][3];
+};
+
+// A lane's place in its block and in the lattice.
+struct SapLane {
+    int lc[4];              // coordinates in the block
+    uint32_t f[4];          // local index without coordinate mu (its place in a mu face)
+    int p;                  // parity
+    uint32_t ih;            // half index
+};
+__device__ __forceinline__ SapLane sap_lane(const SapBlockParams& P, const int* bc, int l) {
+    SapLane a;
+    int r = l, s = 1;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int k = (int)fdiv((uint32_t)r, P.d_b[m]);
+        a.lc[m] = r - k * P.b[m];
+        a.f[m] = (uint32_t)(l - r * s + s * k);
+        r = k;
+        s *= P.b[m];
+    }
+    const int x = bc[0] * P.b[0] + a.lc[0], y = bc[1] * P.b[1] + a.lc[1], z = bc[2] * P.b[2] + a.lc[2],
+              t = bc[3] * P.b[3] + a.lc[3];
+    a.ih = (uint32_t)(x >> 1) + (uint32_t)P.g.lxh * ((uint32_t)y + (uint32_t)P.g.ly *
+                                                     ((uint32_t)z + (uint32_t)P.g.lz * (uint32_t)t));
+    a.p = (x + y + z + t) & 1;
+    return a;
+}
+
+// The block's neighbour d = +-1 along MU, numbered among its colour's blocks:
+// the same compressed coordinates except along MU (the halved direction's
+// coordinate is the same before halving).
+template <int MU>
+__device__ __forceinline__ uint32_t sap_nbr_block(const SapBlockParams& P, const int* bc, int d) {
+    int c[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) c[m] = bc[m];
+    c[MU] += d;
+    if (c[MU] == P.nb[MU]) c[MU] = 0;
+    if (c[MU] < 0) c[MU] = P.nb[MU] - 1;
+    uint32_t a = 0;
+#pragma unroll
+    for (int m = 3; m >= 0; --m) a = a * (uint32_t)P.cb[m] + (uint32_t)(m == P.split ? c[m] >> 1 : c[m]);
+    return a;
+}
+
+// Hops into the block across its two mu faces from the neighbouring blocks'
+// last increments.  The loads of all eight faces are issued first
+// (sap_faces_load), then added (sap_faces_add): a lane waits for memory once
+// instead of once per face.
+struct SapFaceRaw {
+    uint4 up[3], dn[3];     // upper face of the block: from above; lower face: from below
+};
+template <int MU>
+__device__ __forceinline__ void sap_faces_load(const SapBlockParams& P, const uint4* fin, const int* bc,
+                                               const SapLane& a, bool act, SapFaceRaw& w) {
+    if (P.nb[MU] == 1) return;
+    const uint32_t nf = (uint32_t)(P.bvol / P.b[MU]);
+    if (act && a.lc[MU] == P.b[MU] - 1) {
+        const uint4* p = fin + (size_t)sap_nbr_block<MU>(P, bc, 1) * P.fwords + P.foff[MU] + a.f[MU];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w.up[k] = p[k * nf];
+    }
+    if (act && a.lc[MU] == 0) {
+        const uint4* p = fin + (size_t)sap_nbr_block<MU>(P, bc, -1) * P.fwords + P.foff[MU] + 3 * nf + a.f[MU];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w.dn[k] = p[k * nf];
+    }
+}
+template <int MU, class C>
+__device__ __forceinline__ void sap_faces_add(const SapBlockParams& P, const int* bc, const SapLane& a, const C* u,
+                                              bool act, const SapFaceRaw& w, C* acc) {
+    if (P.nb[MU] == 1) return;
+    C h[6], g[6];
+    if (act && a.lc[MU] == P.b[MU] - 1) {       // (1 - gamma_mu) of the block above's lower face
+#pragma unroll
+        for (int k = 0; k < 3; ++k) St<P_F32>::unpack16(w.up[k], h + 2 * k);
+        if (bc[MU] == P.nb[MU] - 1) {
+            const C ph = mk<C>(P.ph[MU][0], P.ph[MU][1]);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) h[k] = mul(ph, h[k]);
+        }
+        half_su3<true>(u, h, g);
+        half_rebuild<MU, 1>(g, 1.0f, acc);
+    }
+    if (act && a.lc[MU] == 0) {                 // U^dag (1 + gamma_mu) of the block below's upper face
+#pragma unroll
+        for (int k = 0; k < 3; ++k) St<P_F32>::unpack16(w.dn[k], g + 2 * k);
+        if (bc[MU] == 0) {
+            const C ph = mk<C>(P.ph[MU][0], -P.ph[MU][1]);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) g[k] = mul(ph, g[k]);
+        }
+        half_rebuild<MU, -1>(g, 1.0f, acc);
+    }
+}
+
+template <int MU, class C>
+__device__ __forceinline__ void sap_faces_out(const SapBlockParams& P, uint4* fout, int lc, uint32_t f, const C* u,
+                                              bool act, const C* e) {
+    if (P.nb[MU] == 1) return;
+    const uint32_t nf = (uint32_t)(P.bvol / P.b[MU]);
+    C h[6], g[6];
+    if (act && lc == 0) {
+        half_project<MU, 1>(e, h);
+        uint4* p = fout + P.foff[MU] + f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[k * nf] = St<P_F32>::pack16(h + 2 * k);
+    }
+    if (act && lc == P.b[MU] - 1) {
+        half_project<MU, -1>(e, h);
+        half_su3<false>(u, h, g);
+        uint4* p = fout + P.foff[MU] + 3 * nf + f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[k * nf] = St<P_F32>::pack16(g + 2 * k);
+    }
+}
+
+// the backward hop of direction MU at its source: U^dag (1 + gamma_mu) res
+template <int MU, int NT, class C>
+__device__ __forceinline__ void sap_bw_out(SapBlockLds<NT>& L, int l, const C* u, const C* res) {
+    C h[6], g[6];
+    half_project<MU, -1>(res, h);
+    half_su3<false>(u, h, g);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) L.bw[MU][k][l] = g[k];
+}
+
+// both hops of direction MU inside the block: jf / jb are the local indices
+// of x +- mu (slot NT where the hop leaves the block)
+template <int MU, int NT, bool WRAP, class C>
+__device__ __forceinline__ void sap_hops(const SapBlockParams& P, const SapBlockLds<NT>& L, int jf, int jb, int lc,
+                                         const C* u, C* q) {
+    C h[6], g[6];
+    {
+        C v[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) v[k] = L.res[k][jf];
+        half_project<MU, 1>(v, h);
+    }
+    if (WRAP && P.wrap[MU]) {
+        const C w = lc == P.b[MU] - 1 ? mk<C>(P.ph[MU][0], P.ph[MU][1]) : mk<C>(1.0f, 0.0f);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) h[k] = mul(w, h[k]);
+    }
+    half_su3<true>(u, h, g);
+    half_rebuild<MU, 1>(g, 1.0f, q);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) g[k] = L.bw[MU][k][jb];
+    if (WRAP && P.wrap[MU]) {
+        const C w = lc == 0 ? mk<C>(P.ph[MU][0], -P.ph[MU][1]) : mk<C>(1.0f, 0.0f);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) g[k] = mul(w, g[k]);
+    }
+    half_rebuild<MU, -1>(g, 1.0f, q);
+}
+
+// WRAP: some direction is spanned by one block and has a phase other than 1.
+template <bool L12, int NT, bool WRAP>
+__global__ void __launch_bounds__(NT, 2) k_sap_block(const SapBlockParams P) {
+    using C = float2;
+    __shared__ SapBlockLds<NT> L;
+    const uint32_t blk = xcd_block(blockIdx.x, gridDim.x, 1);
+    int bc[4];
+    {
+        uint32_t r = blk;
+        int sum = 0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            bc[m] = (int)(r % (uint32_t)P.cb[m]);
+            r /= (uint32_t)P.cb[m];
+            if (m != P.split) sum += bc[m];
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            if (m == P.split) bc[m] = 2 * bc[m] + ((sum + P.colour) & 1);
+    }
+    const int l = threadIdx.x;
+    const bool act = l < P.bvol;
+    const uint32_t n = P.g.vh;
+    const uint32_t cblk = blk + (P.colour ? gridDim.x : 0);             // among all blocks, colour 0 first
+    const size_t field = (size_t)blockIdx.y * P.field_words + (size_t)cblk * 6 * P.bvol;
+    int jf[4], jb[4], lw[4];
+    C u[4][9], res[12], e[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) { res[k] = czero<C>(); e[k] = czero<C>(); }
+    {
+        const SapLane a = sap_lane(P, bc, act ? l : 0);
+        SapFaceRaw fr[4];
+        if (P.fin) {
+            const uint4* fin = P.fin + (size_t)blockIdx.y * P.face_words;
+            sap_faces_load<0>(P, fin, bc, a, act, fr[0]);
+            sap_faces_load<1>(P, fin, bc, a, act, fr[1]);
+            sap_faces_load<2>(P, fin, bc, a, act, fr[2]);
+            sap_faces_load<3>(P, fin, bc, a, act, fr[3]);
+        }
+        if (act) {
+            if (P.eta) {
+                const size_t lat = (size_t)(2 * blockIdx.y + a.p) * P.half_bytes;
+                load_rec<P_F32, 12>(P.eta + lat, n, a.ih, res);
+            } else {
+                sap_load12(P.rho + field + l, (uint32_t)P.bvol, res);
+            }
+        }
+        int s = 1;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int bm = P.b[m], ls = act ? l : 0;
+            const bool cut = P.nb[m] > 1;               // a hop across the block's face leaves it
+            load_link_as<P_F32, L12, false>(P.u + (size_t)(2 * m + a.p) * P.link_block, n, a.ih, u[m]);
+            jf[m] = a.lc[m] + 1 < bm ? ls + s : (cut ? NT : ls - (bm - 1) * s);
+            jb[m] = a.lc[m] > 0 ? ls - s : (cut ? NT : ls + (bm - 1) * s);
+            lw[m] = a.lc[m];
+            s *= bm;
+        }
+        if (P.fin) {
+            C acc[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k) acc[k] = czero<C>();
+            sap_faces_add<0>(P, bc, a, u[0], act, fr[0], acc);
+            sap_faces_add<1>(P, bc, a, u[1], act, fr[1], acc);
+            sap_faces_add<2>(P, bc, a, u[2], act, fr[2], acc);
+            sap_faces_add<3>(P, bc, a, u[3], act, fr[3], acc);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                res[k].x = fma(P.kappa, acc[k].x, res[k].x);
+                res[k].y = fma(P.kappa, acc[k].y, res[k].y);
+            }
+        }
+    }
+    if (l < 12) L.res[l][NT] = czero<C>();
+    if (l < 24) L.bw[l / 6][l % 6][NT] = czero<C>();
+#pragma unroll 1
+    for (int it = 0; it < P.nmr; ++it) {
+        // no lane is still reading the previous step's residual: every lane
+        // passed the barrier of its block sums after its last LDS read
+#pragma unroll
+        for (int k = 0; k < 12; ++k) L.res[k][l] = res[k];
+        sap_bw_out<0>(L, l, u[0], res);
+        __builtin_amdgcn_sched_barrier(0);
+        sap_bw_out<1>(L, l, u[1], res);
+        __builtin_amdgcn_sched_barrier(0);
+        sap_bw_out<2>(L, l, u[2], res);
+        __builtin_amdgcn_sched_barrier(0);
+        sap_bw_out<3>(L, l, u[3], res);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        C q[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) q[k] = czero<C>();
+        sap_hops<0, NT, WRAP>(P, L, jf[0], jb[0], lw[0], u[0], q);
+        __builtin_amdgcn_sched_barrier(0);
+        sap_hops<1, NT, WRAP>(P, L, jf[1], jb[1], lw[1], u[1], q);
+        __builtin_amdgcn_sched_barrier(0);
+        sap_hops<2, NT, WRAP>(P, L, jf[2], jb[2], lw[2], u[2], q);
+        __builtin_amdgcn_sched_barrier(0);
+        sap_hops<3, NT, WRAP>(P, L, jf[3], jb[3], lw[3], u[3], q);
+        __builtin_amdgcn_sched_barrier(0);
+        // q = D_L res = res - kappa H_L res; block sums <q, res>, <q, q>
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            q[k].x = act ? fma(-P.kappa, q[k].x, res[k].x) : 0.0f;
+            q[k].y = act ? fma(-P.kappa, q[k].y, res[k].y) : 0.0f;
+            const double qx = q[k].x, qy = q[k].y, rx = res[k].x, ry = res[k].y;
+            s0 += qx * rx + qy * ry;
+            s1 += qx * ry - qy * rx;
+            s2 += qx * qx + qy * qy;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        s0 = wave_sum_last(s0);
+        s1 = wave_sum_last(s1);
+        s2 = wave_sum_last(s2);
+        if ((l & 63) == 63) { L.red[l >> 6][0] = s0; L.red[l >> 6][1] = s1; L.red[l >> 6][2] = s2; }
+        __syncthreads();
+        double t0 = 0.0, t1 = 0.0, t2 = 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) { t0 += L.red[w][0]; t1 += L.red[w][1]; t2 += L.red[w][2]; }
+        const double inv = t2 > 0.0 ? 1.0 / t2 : 0.0, a0 = t0 * inv, a1 = t1 * inv;
+        const C al = mk<C>((float)a0, (float)a1);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            e[k] = fma_(al, res[k], e[k]);
+            res[k] = sub(res[k], mul(al, q[k]));
+        }
+    }
+    // the lane's place again, from an index the compiler does not know, so that
+    // it holds no register during the steps
+    int l2 = l;
+    asm volatile("" : "+v"(l2));
+    const SapLane a = sap_lane(P, bc, act ? l2 : 0);
+    const size_t lat = (size_t)(2 * blockIdx.y + a.p) * P.half_bytes, bo = field + l2;
+    C v[12];
+    const bool add_to = P.pin != nullptr || P.pin_lat != nullptr;
+    if (add_to && act) {
+        if (P.pin) sap_load12(P.pin + bo, (uint32_t)P.bvol, v);
+        else load_rec<P_F32, 12>(P.pin_lat + lat, n, a.ih, v);
+    }
+    if (P.fout) {
+        uint4* fo = P.fout + (size_t)blockIdx.y * P.face_words + (size_t)blk * P.fwords;
+        sap_faces_out<0>(P, fo, a.lc[0], a.f[0], u[0], act, e);
+        sap_faces_out<1>(P, fo, a.lc[1], a.f[1], u[1], act, e);
+        sap_faces_out<2>(P, fo, a.lc[2], a.f[2], u[2], act, e);
+        sap_faces_out<3>(P, fo, a.lc[3], a.f[3], u[3], act, e);
+    }
+    if (!act) return;
+    if (P.rho_out) sap_store12(P.rho + bo, (uint32_t)P.bvol, res);
+    if (add_to) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) e[k] = add(v[k], e[k]);
+    }
+    if (P.pout) sap_store12(P.pout + bo, (uint32_t)P.bvol, e);
+    else store_rec<P_F32, 12>(P.pout_lat + lat, n, a.ih, e);
 }
 
 }  // namespace weo
@@ -403,9 +803,91 @@ int make_sap_geom(const Geom& g, const int block[4], SapGeom* sg) {
     return 0;
 }
 
+// 16-byte words of one block's projected faces (2 faces of 3 words per site
+// for every direction the lattice is cut in); off[mu]: those before mu.
+static int sap_face_words(const SapGeom& sg, int* off) {
+    int w = 0;
+    for (int m = 0; m < 4; ++m) {
+        if (off) off[m] = w;
+        if (sg.nb[m] > 1) w += 6 * (sg.bvol / sg.b[m]);
+    }
+    return w;
+}
+
+// Whether the faces of all blocks fit two of the three scratch fields (one
+// field is 6 words per site, one colour's faces lie in each): every layout
+// with sum 1 / b_mu <= 2 over the cut directions, so all but blocks of
+// extent 1 in two or more of them.  The others take k_sap_sweep.
+static bool sap_blocks_fit(const SapGeom& sg) { return sap_face_words(sg, nullptr) <= 12 * sg.bvol; }
+
+template <bool L12, bool WRAP>
+static hipError_t sap_block_launch(const SapBlockParams& P, dim3 grid, hipStream_t s) {
+    if (P.bvol <= 64) hipLaunchKernelGGL((k_sap_block<L12, 64, WRAP>), grid, dim3(64), 0, s, P);
+    else if (P.bvol <= 128) hipLaunchKernelGGL((k_sap_block<L12, 128, WRAP>), grid, dim3(128), 0, s, P);
+    else hipLaunchKernelGGL((k_sap_block<L12, 256, WRAP>), grid, dim3(256), 0, s, P);
+    return hipGetLastError();
+}
+
+static hipError_t sap_apply_blocks(const Geom& g, int fmt, const SapGeom& sg, int ncy, int nmr, double kappa,
+                                   const double ph[4][2], const void* u, const void* eta, void* psi, void* rho,
+                                   void* d0, void* d1, int nrhs, hipStream_t s) {
+    const bool two = sg.nblocks > 1;
+    SapBlockParams P;
+    P.g = g;
+    P.split = -1;
+    bool wrap = false;
+    for (int m = 0; m < 4; ++m) {
+        P.b[m] = sg.b[m];
+        P.d_b[m] = make_fastdiv((uint32_t)sg.b[m]);
+        P.nb[m] = P.cb[m] = sg.nb[m];
+        if (P.split < 0 && sg.nb[m] > 1) { P.split = m; P.cb[m] = sg.nb[m] / 2; }
+        P.ph[m][0] = (float)ph[m][0];
+        P.ph[m][1] = (float)ph[m][1];
+        P.wrap[m] = sg.nb[m] == 1 && (ph[m][0] != 1.0 || ph[m][1] != 0.0);
+        wrap = wrap || P.wrap[m];
+    }
+    P.bvol = sg.bvol;
+    P.nmr = nmr;
+    P.kappa = (float)kappa;
+    P.fwords = sap_face_words(sg, P.foff);
+    P.u = static_cast<const uint8_t*>(u);
+    P.link_block = gauge_block_bytes(g, fmt);
+    P.half_bytes = spinor_field_bytes(g, fmt);
+    P.field_words = (size_t)sg.nblocks * sg.bvol * 6;
+    P.face_words = (size_t)(sg.nblocks / 2) * P.fwords;
+    P.rho = static_cast<uint4*>(rho);
+    // Faces within one field (sum 1 / b_mu <= 1, e.g. 4^4): both colours in
+    // d1, the solution in block order in d0 until the last cycle.  Else one
+    // colour in each and the solution in lattice order throughout.
+    const bool small = P.fwords <= 6 * sg.bvol;
+    uint4* face[2] = {small ? static_cast<uint4*>(d1) : static_cast<uint4*>(d0),
+                      small ? static_cast<uint4*>(d1) + (size_t)nrhs * P.face_words : static_cast<uint4*>(d1)};
+    uint4* pblk = small ? static_cast<uint4*>(d0) : nullptr;
+    const dim3 grid((unsigned)(two ? sg.nblocks / 2 : 1), (unsigned)nrhs);
+    for (int cy = 0; cy < ncy; ++cy)
+        for (int c = 0; c < (two ? 2 : 1); ++c) {
+            const bool first = cy == 0, last = cy == ncy - 1;
+            P.colour = c;
+            P.eta = first ? static_cast<const uint8_t*>(eta) : nullptr;
+            P.rho_out = !last;
+            P.fin = two && !(first && c == 0) ? face[1 - c] : nullptr;
+            P.fout = two && !(last && c == 1) ? face[c] : nullptr;
+            P.pin = first ? nullptr : pblk;
+            P.pin_lat = first || pblk ? nullptr : static_cast<const uint8_t*>(psi);
+            P.pout = last ? nullptr : pblk;
+            P.pout_lat = static_cast<uint8_t*>(psi);
+            hipError_t e = hipErrorInvalidValue;
+            if (fmt == FMT_S_S_18) e = wrap ? sap_block_launch<false, true>(P, grid, s) : sap_block_launch<false, false>(P, grid, s);
+            if (fmt == FMT_S_S_12) e = wrap ? sap_block_launch<true, true>(P, grid, s) : sap_block_launch<true, false>(P, grid, s);
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
+}
+
 hipError_t sap_apply(const Geom& g, int fmt, const SapGeom& sg, int ncy, int nmr, double kappa,
                      const double ph[4][2], const void* u, const void* eta, void* psi, void* rho, void* d0,
                      void* d1, int nrhs, hipStream_t s) {
+    if (sap_blocks_fit(sg)) return sap_apply_blocks(g, fmt, sg, ncy, nmr, kappa, ph, u, eta, psi, rho, d0, d1, nrhs, s);
     const size_t bytes = (size_t)nrhs * 2 * spinor_field_bytes(g, fmt);
     hipError_t e = hipMemcpyAsync(rho, eta, bytes, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return e;

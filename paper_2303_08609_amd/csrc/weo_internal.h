@@ -218,7 +218,7 @@ hipError_t launch_sap_sweep(const Geom& g, int fmt, const SapGeom& sg, int colou
 int make_sap_geom(const Geom& g, const int block[4], SapGeom* sg);
 // psi = K eta: ncy SAP cycles (colour 0 then 1) from zero, nmr MR steps per
 // block; nrhs full fields in the FP32 format fmt; rho, d0, d1: nrhs full
-// fields of scratch each.
+// fields of scratch each (eta may not overlap them).
 hipError_t sap_apply(const Geom& g, int fmt, const SapGeom& sg, int ncy, int nmr, double kappa,
                      const double ph[4][2], const void* u, const void* eta, void* psi, void* rho, void* d0,
                      void* d1, int nrhs, hipStream_t s);
