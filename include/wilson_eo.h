@@ -118,14 +118,16 @@ int weo_format_supported(const weo_format* fmt);
  * spinors and links; other formats fall back to -1 / -3).  For these,
  * sites per workgroup is 64, 128 or 256.  nr = -5: the 64 sites' links
  * staged in LDS and shared by `sites` wavefronts (2, 3, 4, 6, 8 or 12;
- * clamped to 4 for FP64 and 8 for FP16/BF16 spinors), each walking every
- * sites-th right-hand side (all formats); here split = 0 sweeps the lattice
- * once for all right-hand sides, split = f in 1..16 once per f of them
- * (the links staged again per sweep).  persist in {0, 1}, bz in -64..64 and
- * split in {0, 1} (for nr > 1) complete the shape.  bz > 0 visits the lattice in strips of bz z-planes, all t per
- * strip; bz < 0 the same in columns of half an (x, y) plane (y below
- * ly / 2, then the rest) times -bz z-planes (both ignored where the lattice
- * or workgroup size does not allow them);
+ * clamped to 8 for FP64 spinors), each walking every sites-th right-hand
+ * side (all formats, and the hops with clover blocks, which take no other
+ * form but nr = 1); here split = 0 sweeps the lattice once for all
+ * right-hand sides, split = f in 1..16 once per f of them (the links staged
+ * again per sweep), and persist has no effect.  persist in {0, 1}, bz in
+ * -64..64 and split in {0, 1} (for nr > 1) complete the shape.  bz > 0
+ * visits the lattice in strips of bz z-planes, all t per strip (the last
+ * strip lower where bz does not divide Lz); bz < 0 the same in columns of
+ * half an (x, y) plane (y below ly / 2, then the rest) times -bz z-planes
+ * (both ignored where the lattice or workgroup size does not allow them);
  * split = 1 gives each group of nr rhs its own workgroups and sweep of the
  * lattice.  Returns WEO_ERR_ARG for other values.  The setting is
  * process-wide. */
@@ -136,7 +138,8 @@ int weo_set_mrhs_shape(int nr, int sites, int persist, int bz, int split);
  * 2 norm partials); returns the untruncated length.  buf may be NULL to
  * query the length.  A multi-rhs launch is tuned on its first call by
  * timing every candidate shape on the caller's stream and buffers, except
- * an in-place axpy (y is out), which runs untuned.  With the environment
+ * an in-place axpy (y is out) and a launch on a stream under capture, which
+ * run untuned.  With the environment
  * variable WILSON_EO_TUNE_CACHE naming a file, tuned shapes are appended to
  * it (a header line with the cache version and GPU architecture, then one
  * text line per key) and read back by later processes, which then skip the

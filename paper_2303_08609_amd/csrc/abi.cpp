@@ -381,7 +381,8 @@ int wilson_eo_clover_hop(const weo_lattice* lat, const weo_format* fmt, int out_
     h.alpha = y ? alpha : 0.0;
     h.partial = nullptr;
     h.nrhs = nrhs;
-    return hip_status(launch_hop_clover(h, clover, static_cast<hipStream_t>(stream)));
+    h.clv = clover;
+    return hip_status(launch_hop(h, static_cast<hipStream_t>(stream)));
 }
 
 int wilson_eo_clover_apply(const weo_lattice* lat, const weo_format* fmt, int dagger, const void* u,

@@ -16,12 +16,13 @@ __global__ void __launch_bounds__(256, Waves<SP>::n > 0 ? Waves<SP>::n : 1) k_ho
     using R = typename Arith<SP>::R;
     using C = cx<R>;
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x, P.remap);
-    const uint32_t ih = block_first_site(P.sched, P.g, blk, blockDim.x) + threadIdx.x;
+    const SiteSpan sp = block_span(P.sched, P.g, blk, blockDim.x);
+    const uint32_t ih = sp.base + threadIdx.x;
     const int rhs = blockIdx.y;
     const uint8_t* in = P.in + (size_t)rhs * P.spinor_bytes;
     uint8_t* out = P.out + (size_t)rhs * P.spinor_bytes;
     double nrm = 0.0, dre = 0.0, dim = 0.0;
-    if (ih < P.g.vh) {
+    if (ih < sp.end) {
         const Site s = decode(P.g, ih, P.out_par);
         const Nbr nb = neighbours(P.g, s);
         C acc[12];
@@ -44,8 +45,9 @@ __global__ void __launch_bounds__(256, Waves<SP>::n > 0 ? Waves<SP>::n : 1) k_ho
     }
     if constexpr (NORM) {
         // one partial per 64-site chunk (one wavefront)
-        const uint32_t chunk = (block_first_site(P.sched, P.g, blk, blockDim.x) + (threadIdx.x & ~63u)) >> 6;
-        hop_partials_out<DOT>(P, (size_t)rhs, chunk, (P.g.vh + 63) >> 6, (threadIdx.x & 63) == 0, nrm, dre, dim);
+        const uint32_t chunk = (sp.base + (threadIdx.x & ~63u)) >> 6;
+        hop_partials_out<DOT>(P, (size_t)rhs, chunk, (P.g.vh + 63) >> 6, (threadIdx.x & 63) == 0 && ih < sp.end,
+                              nrm, dre, dim);
     }
 }
 
@@ -72,10 +74,6 @@ static void read_env_tuning() {
 }
 
 uint32_t hop_partials(const Geom& g) { return (g.vh + 63) / 64; }
-
-static uint32_t hop_blocks(const Geom& g) {
-    return (g.vh + (uint32_t)g_hop_tune.block - 1) / (uint32_t)g_hop_tune.block;
-}
 
 template <int SP, int LP, bool L12>
 static hipError_t launch_fmt(const HopLaunch& h, const HopParams& P, dim3 grid, dim3 block,
@@ -133,9 +131,9 @@ hipError_t launch_hop_single(const HopLaunch& h, hipStream_t s) {
     P.partial = h.partial;
     P.spinor_bytes = spinor_field_bytes(h.g, h.fmt);
     P.link_block = gauge_block_bytes(h.g, h.fmt);
-    P.sched = make_sched(h.g, g_hop_tune.bz, (uint32_t)g_hop_tune.block);
+    P.sched = make_sched(h.g, g_hop_tune.bz, (uint32_t)g_hop_tune.block, h.partial != nullptr);
     const dim3 block(g_hop_tune.block);
-    const dim3 grid(hop_blocks(h.g), h.nrhs);
+    const dim3 grid(P.sched.nblk, h.nrhs);
     switch (h.fmt) {
         case FMT_D_D_18: return launch_fmt<P_F64, P_F64, false>(h, P, grid, block, s);
         case FMT_D_D_12: return launch_fmt<P_F64, P_F64, true>(h, P, grid, block, s);

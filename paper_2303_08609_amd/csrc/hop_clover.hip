@@ -50,12 +50,13 @@ __global__ void __launch_bounds__(256) k_hop_clv(const CloverHopParams Q) {
     using C = cx<R>;
     const HopParams& P = Q.h;
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x, P.remap);
-    const uint32_t ih = block_first_site(P.sched, P.g, blk, blockDim.x) + threadIdx.x;
+    const SiteSpan sp = block_span(P.sched, P.g, blk, blockDim.x);
+    const uint32_t ih = sp.base + threadIdx.x;
     const int rhs = blockIdx.y;
     const uint8_t* in = P.in + (size_t)rhs * P.spinor_bytes;
     uint8_t* out = P.out + (size_t)rhs * P.spinor_bytes;
     double nrm = 0.0;
-    if (ih < P.g.vh) {
+    if (ih < sp.end) {
         const Site s = decode(P.g, ih, P.out_par);
         const Nbr nb = neighbours(P.g, s);
         C acc[12];
@@ -105,9 +106,9 @@ __global__ void __launch_bounds__(256) k_hop_clv(const CloverHopParams Q) {
     }
     if constexpr (NORM) {
         const double t = wave_sum64(nrm);
-        const uint32_t chunk = (block_first_site(P.sched, P.g, blk, blockDim.x) + (threadIdx.x & ~63u)) >> 6;
+        const uint32_t chunk = (sp.base + (threadIdx.x & ~63u)) >> 6;
         const uint32_t nchunk = (P.g.vh + 63) >> 6;
-        if ((threadIdx.x & 63) == 0 && chunk < nchunk) P.partial[(size_t)rhs * nchunk + chunk] = t;
+        if ((threadIdx.x & 63) == 0 && ih < sp.end) P.partial[(size_t)rhs * nchunk + chunk] = t;
     }
 }
 
@@ -131,7 +132,7 @@ static hipError_t clv_fmt(const HopLaunch& h, const CloverHopParams& Q, dim3 gri
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_hop_clover(const HopLaunch& h, const void* clv, hipStream_t s) {
+hipError_t launch_hop_clover_single(const HopLaunch& h, hipStream_t s) {
     const TuneCfg& tc = hop_tune();
     CloverHopParams Q;
     HopParams& P = Q.h;
@@ -152,10 +153,10 @@ hipError_t launch_hop_clover(const HopLaunch& h, const void* clv, hipStream_t s)
     P.partial = h.partial;
     P.spinor_bytes = spinor_field_bytes(h.g, h.fmt);
     P.link_block = gauge_block_bytes(h.g, h.fmt);
-    P.sched = make_sched(h.g, tc.bz, (uint32_t)tc.block);
+    P.sched = make_sched(h.g, tc.bz, (uint32_t)tc.block, h.partial != nullptr);
     Q.block_bytes = clover_block_bytes(h.g, h.fmt);
-    Q.clv = static_cast<const uint8_t*>(clv) + (size_t)(2 * h.out_par) * Q.block_bytes;
-    const dim3 block(tc.block), grid((h.g.vh + (uint32_t)tc.block - 1) / (uint32_t)tc.block, h.nrhs);
+    Q.clv = static_cast<const uint8_t*>(h.clv) + (size_t)(2 * h.out_par) * Q.block_bytes;
+    const dim3 block(tc.block), grid(P.sched.nblk, h.nrhs);
     switch (h.fmt) {
         case FMT_D_D_18: return clv_fmt<P_F64, P_F64, false>(h, Q, grid, block, s);
         case FMT_D_D_12: return clv_fmt<P_F64, P_F64, true>(h, Q, grid, block, s);
@@ -182,20 +183,24 @@ hipError_t launch_apply_clover(const Geom& g, int fmt, const double phase[4][2],
     for (int m = 0; m < 4; ++m) { h.phase[m][0] = phase[m][0]; h.phase[m][1] = phase[m][1]; }
     h.u = u;
     h.nrhs = nrhs;
+    h.fp32 = true;
     hipError_t e;
     if (!dagger) {
+        h.clv = clv;
         // tmp_o = C_o H_oe in;  out = in - kappa^2 C_e H_eo tmp_o
         h.out_par = 1; h.in = in; h.out = tmp; h.y = nullptr; h.alpha = 0.0; h.partial = nullptr;
-        if ((e = launch_hop_clover(h, clv, s)) != hipSuccess) return e;
+        if ((e = launch_hop(h, s)) != hipSuccess) return e;
         h.out_par = 0; h.in = tmp; h.out = out; h.y = in; h.alpha = -kappa * kappa; h.partial = partial;
-        return launch_hop_clover(h, clv, s);
+        return launch_hop(h, s);
     }
     // out = C_e in;  tmp_o = C_o H_oe^dag out;  out = in - kappa^2 H_eo^dag tmp_o
     if ((e = launch_clover_site(g, fmt, 0, clv, in, nullptr, 0.0, out, nrhs, s)) != hipSuccess) return e;
     h.out_par = 1; h.in = out; h.out = tmp; h.y = nullptr; h.alpha = 0.0; h.partial = nullptr;
-    if ((e = launch_hop_clover(h, clv, s)) != hipSuccess) return e;
+    h.clv = clv;
+    if ((e = launch_hop(h, s)) != hipSuccess) return e;
+    h.clv = nullptr;
     h.out_par = 0; h.in = tmp; h.out = out; h.y = in; h.alpha = -kappa * kappa; h.partial = partial;
-    return launch_hop_single(h, s);
+    return launch_hop(h, s);
 }
 
 }  // namespace weo

@@ -33,34 +33,13 @@
 #include <tuple>
 #include <vector>
 
-#include "hop_core.h"
+#include "hop_mrhs.h"
 
 namespace weo {
 
 // The LDS-staged form (k_hop_lw) in MrhsCfg::nr (MrhsCfg::s then holds the
 // wavefronts per workgroup).
 constexpr int kNrLw = -5;
-// Output records of the multi-RHS kernels are written with streaming stores
-// in every precision: with many fields per site the output lines would
-// otherwise take L2 from the input records that the +-z and +-t neighbours
-// read again (FP32/18 and FP16/12 at 12 rhs: 4 % faster).  -D
-// WEO_MRHS_NT_STORE=0 restores regular stores for comparison.
-#ifdef WEO_MRHS_NT_STORE
-template <int SP> constexpr bool mrhs_nt_store() { return WEO_MRHS_NT_STORE != 0; }
-#else
-template <int SP> constexpr bool mrhs_nt_store() { return true; }
-#endif
-#ifndef LW_CROSS
-#define LW_CROSS (SP != P_F64)
-#endif
-
-struct MrhsParams {
-    HopParams h;
-    int nrhs;
-    uint32_t nblk;      // site blocks of blockDim.x sites
-    int rhs_per_row;    // LDS-staged form: right-hand sides per grid row
-};
-
 // Raw words of one neighbour: its link and the NR spinor records.
 template <int SP, int LP, bool L12, int NR>
 struct MrhsRaw {
@@ -152,12 +131,12 @@ __global__ void __launch_bounds__(256) k_hop_mrhs(const MrhsParams M) {
     const uint32_t nchunk = (P.g.vh + 63) >> 6;
     for (uint32_t b = blockIdx.x; b < M.nblk; b += gridDim.x) {
         const uint32_t blk = xcd_block(b, M.nblk, P.remap);
-        const uint32_t base = block_first_site(P.sched, P.g, blk, S);
-        const uint32_t ih = base + threadIdx.x;
+        const SiteSpan sp = block_span(P.sched, P.g, blk, S);
+        const uint32_t base = sp.base, ih = base + threadIdx.x;
         double nrm[NR], dre[NR], dim[NR];
 #pragma unroll
         for (int q = 0; q < NR; ++q) nrm[q] = dre[q] = dim[q] = 0.0;
-        if (ih < P.g.vh && r0 < M.nrhs) {
+        if (ih < sp.end && r0 < M.nrhs) {
             const Site s = decode(P.g, ih, P.out_par);
             const Nbr nb = neighbours(P.g, s);
             C acc[NR][12];
@@ -193,8 +172,8 @@ __global__ void __launch_bounds__(256) k_hop_mrhs(const MrhsParams M) {
 #pragma unroll
             for (int q = 0; q < NR; ++q)
                 if (r0 + q < M.nrhs)          // wave-uniform
-                    hop_partials_out(P, (size_t)(r0 + q), chunk, nchunk, (threadIdx.x & 63) == 0, nrm[q], dre[q],
-                                     dim[q]);
+                    hop_partials_out(P, (size_t)(r0 + q), chunk, nchunk, (threadIdx.x & 63) == 0 && ih < sp.end, nrm[q],
+                                     dre[q], dim[q]);
         }
     }
 }
@@ -246,15 +225,14 @@ __device__ __forceinline__ void lr_consume(const HopParams& P, const Nbr& nb,
 // right-hand side prefetch the first D records of the next.
 template <int SP, int LP, bool L12, bool DAG, bool CPH, int D, int K, class C>
 __device__ __forceinline__ void lr_step(const HopParams& P, const uint8_t* in, const uint8_t* in_next,
-                                        const Nbr& nb,
+                                        const Nbr& nb, const NbrOff& no,
                                         const RawRec<LP, L12 ? 6 : 9, hop_nt<SP>()> (&lk)[8],
                                         RawRec<SP, 12> (&ring)[D + 1], C* acc) {
-    if constexpr (K + D < 8) ring[(K + D) % (D + 1)].load(in, P.g.vh, nb.i[K + D]);
-    else ring[(K + D) % (D + 1)].load(in_next, P.g.vh, nb.i[K + D - 8]);
+    load_spinor<SP>(K + D < 8 ? in : in_next, P.g.vh, no.o[(K + D) & 7], ring[(K + D) % (D + 1)]);
     __builtin_amdgcn_sched_barrier(0);
     lr_consume<SP, LP, L12, DAG, CPH, K>(P, nb, lk[K], ring[K % (D + 1)], acc);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (K + 1 < 8) lr_step<SP, LP, L12, DAG, CPH, D, K + 1>(P, in, in_next, nb, lk, ring, acc);
+    if constexpr (K + 1 < 8) lr_step<SP, LP, L12, DAG, CPH, D, K + 1>(P, in, in_next, nb, no, lk, ring, acc);
 }
 
 template <int SP, int LP, bool L12, bool DAG, bool CPH, int D>
@@ -268,10 +246,11 @@ __global__ void __launch_bounds__(256) k_hop_lr(const MrhsParams M) {
     const uint32_t nchunk = (n + 63) >> 6;
     for (uint32_t b = blockIdx.x; b < M.nblk; b += gridDim.x) {
         const uint32_t blk = xcd_block(b, M.nblk, P.remap);
-        const uint32_t base = block_first_site(P.sched, P.g, blk, S);
-        const uint32_t ih = base + threadIdx.x;
-        const bool valid = ih < n;
+        const SiteSpan sp = block_span(P.sched, P.g, blk, S);
+        const uint32_t base = sp.base, ih = base + threadIdx.x;
+        const bool valid = ih < sp.end;
         Nbr nb;
+        NbrOff no;
         RawRec<LP, L12 ? 6 : 9, hop_nt<SP>()> lk[8];
         RawRec<SP, 12> ring[D + 1];
         if (valid) {
@@ -284,10 +263,13 @@ __global__ void __launch_bounds__(256) k_hop_lr(const MrhsParams M) {
                 lk[k].load(P.u + (size_t)(2 * mu + (fwd ? P.out_par : 1 - P.out_par)) * P.link_block, n,
                            fwd ? ih : nb.i[k]);
             }
+            no.set(nb);
 #pragma unroll
             for (int k = 0; k < D; ++k) ring[k].load(P.in, n, nb.i[k]);
         }
-        for (int r = 0; r < M.nrhs; ++r) {
+        for (int rr = 0; rr < M.nrhs; ++rr) {
+            const int r = opaque_uniform(rr);
+            no.pin();
             double nrm = 0.0, dre = 0.0, dim = 0.0;
             if (valid) {
                 // keep the links as raw words across the loop: without this the
@@ -301,169 +283,14 @@ __global__ void __launch_bounds__(256) k_hop_lr(const MrhsParams M) {
                 C acc[12];
 #pragma unroll
                 for (int k = 0; k < 12; ++k) acc[k] = czero<C>();
-                lr_step<SP, LP, L12, DAG, CPH, D, 0>(P, in, in_next, nb, lk, ring, acc);
+                lr_step<SP, LP, L12, DAG, CPH, D, 0>(P, in, in_next, nb, no, lk, ring, acc);
                 if (P.y) hop_addends<SP>(P, (size_t)r, ih, acc);
                 store_rec<SP, 12, C, mrhs_nt_store<SP>()>(P.out + (size_t)r * P.spinor_bytes, n, ih, acc);
                 if (P.partial) hop_reduce<SP>(P, (size_t)r, ih, acc, nrm, dre, dim);
             }
             if (P.partial)
-                hop_partials_out(P, (size_t)r, (base + (threadIdx.x & ~63u)) >> 6, nchunk, (threadIdx.x & 63) == 0, nrm,
-                                 dre, dim);
-        }
-    }
-}
-
-// ---- links staged in LDS, right-hand sides across wavefronts --------------------
-// A workgroup of W wavefronts owns 64 output sites.  The wavefronts first
-// copy the raw words of the 64 sites' 8 links from memory into LDS (each
-// wavefront some of the directions), then each walks its own right-hand
-// sides (w, w + W, ...) with the single-rhs pipeline, taking the links from
-// LDS.  Every link is read from memory once per launch, as in the
-// link-resident form, but the links occupy LDS shared by W wavefronts
-// instead of registers of each lane, so the register footprint is the
-// single-rhs kernel's: this is the form that exists for FP64 (whose 8 links
-// do not fit a lane's registers next to its pipeline), and a candidate for
-// the other formats.  LDS holds the links as [direction][16-byte slot][site]
-// (a tail of 4 or 8 bytes takes a whole slot), so the 64 lanes of a read
-// touch 1 KiB of consecutive words.
-template <int SP, int LP, bool L12> struct LwShape {
-    using LRaw = RawRec<LP, L12 ? 6 : 9, hop_nt<SP>()>;
-    static constexpr int NC = Rec<LP, L12 ? 6 : 9>::NFULL;
-    static constexpr int TB = Rec<LP, L12 ? 6 : 9>::TAILB;
-    static constexpr int NS = NC + (TB ? 1 : 0);     // 16-byte slots per link
-    static constexpr int LDS_U4 = 8 * NS * 64;
-};
-
-template <int SP, int LP, bool L12>
-__device__ __forceinline__ void lw_put(uint4* lds, int k, uint32_t lane,
-                                       const typename LwShape<SP, LP, L12>::LRaw& r) {
-    using Sh = LwShape<SP, LP, L12>;
-#pragma unroll
-    for (int p = 0; p < Sh::NC; ++p) lds[(k * Sh::NS + p) * 64 + lane] = r.w[p];
-    if constexpr (Sh::TB == 8) lds[(k * Sh::NS + Sh::NC) * 64 + lane] = make_uint4(r.t8.x, r.t8.y, 0u, 0u);
-    if constexpr (Sh::TB == 4) lds[(k * Sh::NS + Sh::NC) * 64 + lane] = make_uint4(r.t4, 0u, 0u, 0u);
-}
-
-template <int SP, int LP, bool L12>
-__device__ __forceinline__ void lw_get(const uint4* lds, int k, uint32_t lane,
-                                       typename LwShape<SP, LP, L12>::LRaw& r) {
-    using Sh = LwShape<SP, LP, L12>;
-#pragma unroll
-    for (int p = 0; p < Sh::NC; ++p) r.w[p] = lds[(k * Sh::NS + p) * 64 + lane];
-    if constexpr (Sh::TB == 8) {
-        const uint4 v = lds[(k * Sh::NS + Sh::NC) * 64 + lane];
-        r.t8 = make_uint2(v.x, v.y);
-    }
-    if constexpr (Sh::TB == 4) r.t4 = lds[(k * Sh::NS + Sh::NC) * 64 + lane].x;
-}
-
-template <int SP> constexpr int lw_depth() { return 1; }
-// Most wavefronts per workgroup: FP64 keeps the single-rhs register budget
-// (256 VGPRs, as the FP64 single-rhs hop), so at most 4; FP32 fits 3 waves
-// per SIMD at up to 12; FP16 / BF16 at up to 8 (12 spills a little).
-template <int SP> constexpr int lw_maxw() { return SP == P_F64 ? 4 : (SP == P_F32 ? 12 : 8); }
-// Prefetch of the next right-hand side's first records across the epilogue
-// (off for FP64: its records held through the epilogue spill).
-template <int SP> constexpr bool lw_cross() { return LW_CROSS; }
-
-template <int SP, int LP, bool L12> struct LwSlot {
-    RawRec<SP, 12> sp;
-    typename LwShape<SP, LP, L12>::LRaw ln;
-};
-
-// Ring of D+1 slots as in the link-resident form: the neighbour record and
-// the link words of direction K + D are fetched while direction K is
-// computed; the last D directions of one right-hand side fetch the first
-// records of the next.
-template <int SP, int LP, bool L12, bool DAG, bool CPH, int D, int K, class C>
-__device__ __forceinline__ void lw_step(const HopParams& P, const uint4* lds, uint32_t lane, const uint8_t* in,
-                                        const uint8_t* in_next, const Nbr& nb, LwSlot<SP, LP, L12> (&ring)[D + 1],
-                                        C* acc) {
-    constexpr int KN = (K + D) & 7;
-    if constexpr (K + D < 8 || lw_cross<SP>()) {
-        LwSlot<SP, LP, L12>& nx = ring[(K + D) % (D + 1)];
-        nx.sp.load(K + D < 8 ? in : in_next, P.g.vh, nb.i[KN]);
-        lw_get<SP, LP, L12>(lds, KN, lane, nx.ln);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    lr_consume<SP, LP, L12, DAG, CPH, K>(P, nb, ring[K % (D + 1)].ln, ring[K % (D + 1)].sp, acc);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (K + 1 < 8) lw_step<SP, LP, L12, DAG, CPH, D, K + 1>(P, lds, lane, in, in_next, nb, ring, acc);
-}
-
-
-template <int SP, int LP, bool L12, bool DAG, bool CPH, bool DOT>
-__global__ void __launch_bounds__(64 * lw_maxw<SP>()) k_hop_lw(const MrhsParams M) {
-    using R = typename Arith<SP>::R;
-    using C = cx<R>;
-    using Sh = LwShape<SP, LP, L12>;
-    constexpr int D = lw_depth<SP>();
-    __shared__ uint4 lds[Sh::LDS_U4];
-    const HopParams& P = M.h;
-    const uint32_t n = P.g.vh;
-    const uint32_t nchunk = (n + 63) >> 6;
-    const uint32_t lane = threadIdx.x;                    // blockDim.x == 64
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
-    const int W = (int)blockDim.y;
-    // this grid row's right-hand sides [r0, r1): rows are separate sweeps
-    const int r0 = (int)blockIdx.y * M.rhs_per_row;
-    const int r1 = r0 + M.rhs_per_row < M.nrhs ? r0 + M.rhs_per_row : M.nrhs;
-    for (uint32_t b = blockIdx.x; b < M.nblk; b += gridDim.x) {
-        const uint32_t blk = xcd_block(b, M.nblk, P.remap);
-        const uint32_t base = block_first_site(P.sched, P.g, blk, 64);
-        const uint32_t ih = base + lane;
-        const bool valid = ih < n;
-        Nbr nb;
-        if (valid) nb = neighbours(P.g, decode(P.g, ih, P.out_par));
-        __syncthreads();                                  // the previous block's links are consumed
-        if (valid) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (k % W != wv) continue;                // wave-uniform
-                const int mu = k >> 1;
-                const bool fwd = (k & 1) == 0;
-                typename Sh::LRaw r;
-                r.load(P.u + (size_t)(2 * mu + (fwd ? P.out_par : 1 - P.out_par)) * P.link_block, n,
-                       fwd ? ih : nb.i[k]);
-                lw_put<SP, LP, L12>(lds, k, lane, r);
-            }
-        }
-        __syncthreads();
-        LwSlot<SP, LP, L12> ring[D + 1];
-        if (lw_cross<SP>() && valid && r0 + wv < r1) {
-            const uint8_t* in0 = P.in + (size_t)(r0 + wv) * P.spinor_bytes;
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                ring[k].sp.load(in0, n, nb.i[k]);
-                lw_get<SP, LP, L12>(lds, k, lane, ring[k].ln);
-            }
-        }
-        for (int r = r0 + wv; r < r1; r += W) {
-            double nrm = 0.0, dre = 0.0, dim = 0.0;
-            if (valid) {
-                const uint8_t* in = P.in + (size_t)r * P.spinor_bytes;
-                if constexpr (!lw_cross<SP>()) {
-#pragma unroll
-                    for (int k = 0; k < D; ++k) {
-                        ring[k].sp.load(in, n, nb.i[k]);
-                        lw_get<SP, LP, L12>(lds, k, lane, ring[k].ln);
-                    }
-                }
-                const uint8_t* in_next = r + W < r1 ? in + (size_t)W * P.spinor_bytes : in;
-                // an opaque copy of the lane index per right-hand side: the LDS
-                // link words are invariant in this loop, and without it the
-                // compiler hoists all 8 links' reads out of it into registers
-                uint32_t lo = lane;
-                asm volatile("" : "+v"(lo));
-                C acc[12];
-#pragma unroll
-                for (int k = 0; k < 12; ++k) acc[k] = czero<C>();
-                lw_step<SP, LP, L12, DAG, CPH, D, 0>(P, lds, lo, in, in_next, nb, ring, acc);
-                if (P.y) hop_addends<SP>(P, (size_t)r, ih, acc);
-                store_rec<SP, 12, C, mrhs_nt_store<SP>()>(P.out + (size_t)r * P.spinor_bytes, n, ih, acc);
-                if (P.partial) hop_reduce<SP, DOT>(P, (size_t)r, ih, acc, nrm, dre, dim);
-            }
-            if (P.partial) hop_partials_out<DOT>(P, (size_t)r, base >> 6, nchunk, lane == 0, nrm, dre, dim);
+                hop_partials_out(P, (size_t)r, (base + (threadIdx.x & ~63u)) >> 6, nchunk,
+                                 (threadIdx.x & 63) == 0 && valid, nrm, dre, dim);
         }
     }
 }
@@ -485,54 +312,6 @@ __global__ void __launch_bounds__(64 * lw_maxw<SP>()) k_hop_lw(const MrhsParams 
 // site).  The projected half spinor and the rebuilt row are rounded to FP16
 // (relative 2^-11, the storage precision of the inputs); products and sums
 // are FP32.
-typedef _Float16 h2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ h2v h2v_of(uint32_t w) { return __builtin_bit_cast(h2v, w); }
-__device__ __forceinline__ uint32_t u32_of(h2v v) { return __builtin_bit_cast(uint32_t, v); }
-__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
-    return __builtin_amdgcn_fdot2(h2v_of(a), h2v_of(b), c, false);
-}
-__device__ __forceinline__ uint32_t swap_pair(uint32_t w) { return __builtin_amdgcn_alignbit(w, w, 16); }
-
-struct Link16 {
-    uint32_t e[9];       // U_ab as FP16 pairs, row-major
-};
-
-// Link of direction k of the site (raw FP16 words), third row rebuilt for
-// 12 reals, boundary phase ph folded in on edge hops (ph U forward,
-// (ph U)^dag = conj(ph) U^dag backward, so the stored link is ph U either way).
-template <bool L12, bool CPH>
-__device__ __forceinline__ void link16_load(const uint8_t* base, uint32_t n, uint32_t i, bool edge, float2 ph,
-                                            Link16& L) {
-    RawRec<P_F16, L12 ? 6 : 9, true> r;
-    r.load(base, n, i);
-    constexpr int NW = L12 ? 6 : 9;
-    uint32_t w[9];
-#pragma unroll
-    for (int p = 0; p < Rec<P_F16, NW>::NFULL; ++p) {
-        w[4 * p] = r.w[p].x; w[4 * p + 1] = r.w[p].y; w[4 * p + 2] = r.w[p].z; w[4 * p + 3] = r.w[p].w;
-    }
-    if constexpr (Rec<P_F16, NW>::TAILB == 8) { w[4 * Rec<P_F16, NW>::NFULL] = r.t8.x; w[4 * Rec<P_F16, NW>::NFULL + 1] = r.t8.y; }
-    if constexpr (Rec<P_F16, NW>::TAILB == 4) w[4 * Rec<P_F16, NW>::NFULL] = r.t4;
-    if constexpr (L12) {
-        float2 u[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) u[k] = h2_to_f2(w[k]);
-        w[6] = f2_to_h2(conj_(sub(mul(u[1], u[5]), mul(u[2], u[4]))));
-        w[7] = f2_to_h2(conj_(sub(mul(u[2], u[3]), mul(u[0], u[5]))));
-        w[8] = f2_to_h2(conj_(sub(mul(u[0], u[4]), mul(u[1], u[3]))));
-    }
-    if constexpr (CPH) {
-        const float2 f = edge ? ph : make_float2(1.f, 0.f);
-#pragma unroll
-        for (int k = 0; k < 9; ++k) L.e[k] = f2_to_h2(mul(f, h2_to_f2(w[k])));
-    } else {
-        // a real phase +-1: a sign flip of both halves where it is -1
-        const uint32_t flip = (edge && ph.x < 0.f) ? 0x80008000u : 0u;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) L.e[k] = w[k] ^ flip;
-    }
-}
-
 // One direction on a neighbour record p (12 FP16 pairs, [spin][colour]):
 // project with (1 - S gamma_mu), multiply by U (FWD) or U^dag, rebuild and
 // accumulate in FP32 (the rules of hop_dir).
@@ -611,26 +390,20 @@ __device__ __forceinline__ void h16_dir(const uint32_t* p, const Link16& L, floa
     }
 }
 
-__device__ __forceinline__ void rec16_words(const RawRec<P_F16, 12>& r, uint32_t* p) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) { p[4 * q] = r.w[q].x; p[4 * q + 1] = r.w[q].y; p[4 * q + 2] = r.w[q].z; p[4 * q + 3] = r.w[q].w; }
-}
-
 template <bool DAG, int D, int K>
 __device__ __forceinline__ void h16_step(const HopParams& P, const uint8_t* in, const uint8_t* in_next,
-                                         const Nbr& nb, const Link16 (&lk)[8], RawRec<P_F16, 12> (&ring)[D + 1],
+                                         const NbrOff& no, const Link16 (&lk)[8], RawRec<P_F16, 12> (&ring)[D + 1],
                                          float2* acc) {
     constexpr int MU = K / 2;
     constexpr int SF = DAG ? -1 : 1;
-    if constexpr (K + D < 8) ring[(K + D) % (D + 1)].load(in, P.g.vh, nb.i[K + D]);
-    else ring[(K + D) % (D + 1)].load(in_next, P.g.vh, nb.i[K + D - 8]);
+    load_spinor<P_F16>(K + D < 8 ? in : in_next, P.g.vh, no.o[(K + D) & 7], ring[(K + D) % (D + 1)]);
     __builtin_amdgcn_sched_barrier(0);
     uint32_t p[12];
     rec16_words(ring[K % (D + 1)], p);
     if constexpr ((K & 1) == 0) h16_dir<MU, SF, true>(p, lk[K], acc);
     else h16_dir<MU, -SF, false>(p, lk[K], acc);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (K + 1 < 8) h16_step<DAG, D, K + 1>(P, in, in_next, nb, lk, ring, acc);
+    if constexpr (K + 1 < 8) h16_step<DAG, D, K + 1>(P, in, in_next, no, lk, ring, acc);
 }
 
 template <bool L12, bool DAG, bool CPH, int D>
@@ -642,10 +415,11 @@ __global__ void __launch_bounds__(256) k_hop_lr16(const MrhsParams M) {
     const uint32_t nchunk = (n + 63) >> 6;
     for (uint32_t b = blockIdx.x; b < M.nblk; b += gridDim.x) {
         const uint32_t blk = xcd_block(b, M.nblk, P.remap);
-        const uint32_t base = block_first_site(P.sched, P.g, blk, S);
-        const uint32_t ih = base + threadIdx.x;
-        const bool valid = ih < n;
+        const SiteSpan sp = block_span(P.sched, P.g, blk, S);
+        const uint32_t base = sp.base, ih = base + threadIdx.x;
+        const bool valid = ih < sp.end;
         Nbr nb;
+        NbrOff no;
         Link16 lk[8];
         RawRec<P_F16, 12> ring[D + 1];
         if (valid) {
@@ -660,10 +434,13 @@ __global__ void __launch_bounds__(256) k_hop_lr16(const MrhsParams M) {
                 link16_load<L12, CPH>(P.u + (size_t)(2 * mu + (fwd ? P.out_par : 1 - P.out_par)) * P.link_block, n,
                                       fwd ? ih : nb.i[k], nb.edge[k], ph, lk[k]);
             }
+            no.set(nb);
 #pragma unroll
             for (int k = 0; k < D; ++k) ring[k].load(P.in, n, nb.i[k]);
         }
-        for (int r = 0; r < M.nrhs; ++r) {
+        for (int rr = 0; rr < M.nrhs; ++rr) {
+            const int r = opaque_uniform(rr);
+            no.pin();
             double nrm = 0.0, dre = 0.0, dim = 0.0;
             if (valid) {
                 // keep the link words as they are across the loop
@@ -676,14 +453,14 @@ __global__ void __launch_bounds__(256) k_hop_lr16(const MrhsParams M) {
                 float2 acc[12];
 #pragma unroll
                 for (int k = 0; k < 12; ++k) acc[k] = make_float2(0.f, 0.f);
-                h16_step<DAG, D, 0>(P, in, in_next, nb, lk, ring, acc);
+                h16_step<DAG, D, 0>(P, in, in_next, no, lk, ring, acc);
                 if (P.y) hop_addends<P_F16>(P, (size_t)r, ih, acc);
                 store_rec<P_F16, 12, float2, mrhs_nt_store<P_F16>()>(P.out + (size_t)r * P.spinor_bytes, n, ih, acc);
                 if (P.partial) hop_reduce<P_F16>(P, (size_t)r, ih, acc, nrm, dre, dim);
             }
             if (P.partial)
-                hop_partials_out(P, (size_t)r, (base + (threadIdx.x & ~63u)) >> 6, nchunk, (threadIdx.x & 63) == 0, nrm,
-                                 dre, dim);
+                hop_partials_out(P, (size_t)r, (base + (threadIdx.x & ~63u)) >> 6, nchunk,
+                                 (threadIdx.x & 63) == 0 && valid, nrm, dre, dim);
         }
     }
 }
@@ -759,8 +536,7 @@ static hipError_t lr_fmt(const HopLaunch& h, const MrhsParams& M, int depth, dim
 
 template <bool L12, int D>
 static hipError_t lr16_depth(const HopLaunch& h, const MrhsParams& M, dim3 grid, dim3 block, hipStream_t s) {
-    bool cph = false;
-    for (int m = 0; m < 4; ++m) cph = cph || h.phase[m][1] != 0.0;
+    const bool cph = !phases_are_signs(h);
 #define WEO_LR16(DG, CP) hipLaunchKernelGGL((k_hop_lr16<L12, DG, CP, D>), grid, block, 0, s, M)
     if (h.dagger) { if (cph) WEO_LR16(true, true); else WEO_LR16(true, false); }
     else { if (cph) WEO_LR16(false, true); else WEO_LR16(false, false); }
@@ -797,77 +573,37 @@ static hipError_t launch_hop_lr(const HopLaunch& h, const MrhsParams& M, int dep
 
 bool lr_supported(int fmt) { return fmt_info(fmt).spinor_prec != P_F64; }
 
-template <int SP, int LP, bool L12>
-static hipError_t lw_fmt(const HopLaunch& h, const MrhsParams& M, dim3 grid, dim3 block, hipStream_t s) {
-    bool cph = false;
-    for (int m = 0; m < 4; ++m) cph = cph || h.phase[m][1] != 0.0;
-#define WEO_LW(DG, CP, DT) hipLaunchKernelGGL((k_hop_lw<SP, LP, L12, DG, CP, DT>), grid, block, 0, s, M)
-    if (h.dmode) {
-        if (!h.partial) return hipErrorInvalidValue;
-        if (h.dagger) { if (cph) WEO_LW(true, true, true); else WEO_LW(true, false, true); }
-        else { if (cph) WEO_LW(false, true, true); else WEO_LW(false, false, true); }
-    } else {
-        if (h.dagger) { if (cph) WEO_LW(true, true, false); else WEO_LW(true, false, false); }
-        else { if (cph) WEO_LW(false, true, false); else WEO_LW(false, false, false); }
-    }
-#undef WEO_LW
-    return hipGetLastError();
-}
-
-static int lw_max_waves(int fmt) {
-    switch (fmt_info(fmt).spinor_prec) {
-        case P_F64: return lw_maxw<P_F64>();
-        case P_F32: return lw_maxw<P_F32>();
-        default: return lw_maxw<P_F16>();
-    }
-}
-
-// LDS-staged form: W wavefronts of 64 sites per workgroup
-static hipError_t launch_hop_lw(const HopLaunch& h, const MrhsParams& M, int W, dim3 grid, hipStream_t s) {
-    if (W > lw_max_waves(h.fmt)) return hipErrorInvalidValue;
-    const dim3 block(64, (unsigned)W);
-    switch (h.fmt) {
-        case FMT_D_D_18: return lw_fmt<P_F64, P_F64, false>(h, M, grid, block, s);
-        case FMT_D_D_12: return lw_fmt<P_F64, P_F64, true>(h, M, grid, block, s);
-        case FMT_S_S_18: return lw_fmt<P_F32, P_F32, false>(h, M, grid, block, s);
-        case FMT_S_S_12: return lw_fmt<P_F32, P_F32, true>(h, M, grid, block, s);
-        case FMT_H_H_18: return lw_fmt<P_F16, P_F16, false>(h, M, grid, block, s);
-        case FMT_H_H_12: return lw_fmt<P_F16, P_F16, true>(h, M, grid, block, s);
-        case FMT_B_H_18: return lw_fmt<P_BF16, P_F16, false>(h, M, grid, block, s);
-        case FMT_B_H_12: return lw_fmt<P_BF16, P_F16, true>(h, M, grid, block, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 bool lw_waves_ok(int w) { return w == 2 || w == 3 || w == 4 || w == 6 || w == 8 || w == 12; }
 
 hipError_t launch_hop_mrhs(const HopLaunch& h, const MrhsCfg& c, hipStream_t s) {
     MrhsParams M;
     M.h = hop_params(h);
     M.rhs_per_row = h.nrhs;
-    if (c.nr == kNrLw) {
+    M.clv = nullptr;
+    M.block_bytes = 0;
+    if (h.clv) {
+        if (c.nr != kNrLw) return hipErrorInvalidValue;
+        M.block_bytes = clover_block_bytes(h.g, h.fmt);
+        M.clv = static_cast<const uint8_t*>(h.clv) + (size_t)(2 * h.out_par) * M.block_bytes;
+    }
+    if (c.nr == kNrLw || c.nr == kNrLw16 || c.nr == kNrLw16Deep) {
         // LDS-staged: 64 sites per workgroup, c.s wavefronts
         if (!lw_waves_ok(c.s)) return hipErrorInvalidValue;
-        M.h.sched = make_sched(h.g, c.bz, 64u);
+        M.h.sched = make_sched(h.g, c.bz, 64u, h.partial != nullptr);
         M.nrhs = h.nrhs;
-        M.nblk = (h.g.vh + 63u) / 64u;
+        M.nblk = M.h.sched.nblk;
         // c.split = right-hand sides per sweep (0: all in one); each sweep
         // is a grid row and stages the links again
         M.rhs_per_row = c.split > 0 && c.split < h.nrhs ? c.split : h.nrhs;
         const unsigned rows = (unsigned)((h.nrhs + M.rhs_per_row - 1) / M.rhs_per_row);
-        uint32_t nwg = M.nblk;
-        if (c.persist) {
-            const uint32_t cap = 8u * 256u;
-            if (nwg > cap) nwg = cap;
-            nwg = ((nwg + 7u) / 8u) * 8u;
-        }
-        return launch_hop_lw(h, M, c.s, dim3(nwg, rows), s);
+        if (c.nr != kNrLw) return launch_hop_lw16(h, M, c.s, c.nr == kNrLw16Deep ? 3 : 1, dim3(M.nblk, rows), s);
+        return launch_hop_lw(h, M, c.s, dim3(M.nblk, rows), s);    // never persistent
     }
-    M.h.sched = make_sched(h.g, c.bz, (uint32_t)c.s);
+    M.h.sched = make_sched(h.g, c.bz, (uint32_t)c.s, h.partial != nullptr);
     if (c.nr < 0) {
         // link-resident: one lane per site, all rhs in turn; -nr is the ring depth
         M.nrhs = h.nrhs;
-        M.nblk = (h.g.vh + (uint32_t)c.s - 1) / (uint32_t)c.s;
+        M.nblk = M.h.sched.nblk;
         uint32_t nwg = M.nblk;
         if (c.persist) {
             const uint32_t cap = 8u * 256u;
@@ -880,7 +616,7 @@ hipError_t launch_hop_mrhs(const HopLaunch& h, const MrhsCfg& c, hipStream_t s) 
         return launch_hop_lr(h, M, -c.nr, dim3(nwg), dim3((unsigned)c.s), s);
     }
     M.nrhs = h.nrhs;
-    M.nblk = (h.g.vh + (uint32_t)c.s - 1) / (uint32_t)c.s;
+    M.nblk = M.h.sched.nblk;
     const int groups = (h.nrhs + c.nr - 1) / c.nr;
     int gy = c.split ? 1 : 256 / c.s;
     if (gy > groups) gy = groups;
@@ -925,26 +661,33 @@ std::vector<MrhsCfg> candidates(const HopLaunch& h) {
     std::vector<MrhsCfg> v;
     v.push_back({1, 0, 0, 0, 0});
     const bool wide = fmt_info(h.fmt).spinor_prec == P_F64;
-    const bool dot = h.dmode != 0;      // the fused dot: single-rhs and LDS-staged kernels only
+    // the fused dot and the clover blocks: single-rhs and LDS-staged kernels only
+    const bool dot = h.dmode != 0 || h.clv != nullptr;
     if (lr_supported(h.fmt) && !dot)
         for (int s : {64, 128, 256})
             for (int persist : {0, 1})
                 for (int bz : {0, 2, 4, 8}) {
-                    if (bz && make_sched(h.g, bz, (uint32_t)s).bz != bz) continue;
+                    if (bz && make_sched(h.g, bz, (uint32_t)s, h.partial != nullptr).bz != bz) continue;
                     for (int nr : {-1, -3}) v.push_back({nr, s, persist, bz, 0});
-                    if (lr16_supported(h.fmt))
+                    if (lr16_supported(h.fmt) && !h.fp32)
                         for (int nr : {-2, -4}) v.push_back({nr, s, persist, bz, 0});
                 }
+    int w0 = 0;
     for (int w : {2, 3, 4, 6, 8, 12}) {
-        if (w > h.nrhs || w > lw_max_waves(h.fmt)) continue;
-        for (int persist : {0, 1})
-            for (int bz : {0, 2, 4, 8}) {
-                if (bz && make_sched(h.g, bz, 64u).bz != bz) continue;
-                for (int f : {0, 6}) {                // right-hand sides per sweep (0: all)
-                    if (f && (f >= h.nrhs || f < w)) continue;
-                    v.push_back({kNrLw, w, persist, bz, f});
+        // up to the first that holds every right-hand side at once
+        if (w0 >= h.nrhs || w > lw_max_waves(h.fmt)) continue;
+        w0 = w;
+        for (int bz : {0, 2, 4, 8}) {
+            if (bz && make_sched(h.g, bz, 64u, h.partial != nullptr).bz != bz) continue;
+            for (int f : {0, 6}) {                // right-hand sides per sweep (0: all)
+                if (f && (f >= h.nrhs || f < w)) continue;
+                v.push_back({kNrLw, w, 0, bz, f});
+                if (lr16_supported(h.fmt) && !h.fp32 && !dot) {
+                    v.push_back({kNrLw16, w, 0, bz, f});
+                    v.push_back({kNrLw16Deep, w, 0, bz, f});
                 }
             }
+        }
     }
     const int nrs[] = {2, 3, 4, 6};
     for (int nr : nrs) {
@@ -952,7 +695,7 @@ std::vector<MrhsCfg> candidates(const HopLaunch& h) {
         for (int s : {64, 128, 256})
             for (int persist : {0, 1})
                 for (int bz : {0, 2, 4, 8}) {
-                    if (bz && make_sched(h.g, bz, (uint32_t)s).bz != bz) continue;
+                    if (bz && make_sched(h.g, bz, (uint32_t)s, h.partial != nullptr).bz != bz) continue;
                     v.push_back({nr, s, persist, bz, 0});
                     const int groups = (h.nrhs + nr - 1) / nr;
                     if (groups > 1 && s < 256) v.push_back({nr, s, persist, bz, 1});
@@ -961,8 +704,12 @@ std::vector<MrhsCfg> candidates(const HopLaunch& h) {
     return v;
 }
 
+hipError_t run_single(const HopLaunch& h, hipStream_t s) {
+    return h.clv ? launch_hop_clover_single(h, s) : launch_hop_single(h, s);
+}
+
 hipError_t run_cfg(const HopLaunch& h, const MrhsCfg& c, hipStream_t s) {
-    return c.nr == 1 ? launch_hop_single(h, s) : launch_hop_mrhs(h, c, s);
+    return c.nr == 1 ? run_single(h, s) : launch_hop_mrhs(h, c, s);
 }
 
 bool tuning_enabled() {
@@ -984,7 +731,7 @@ bool tuning_verbose() {
 // An entry is used only if its shape is among the current candidates for
 // that key (so a stale or edited file can pick a slower shape, never an
 // invalid launch).  New results are appended, one line per write.
-constexpr int kTuneCacheVersion = 4;
+constexpr int kTuneCacheVersion = 5;
 
 const char* tune_cache_path() {
     const char* p = getenv("WILSON_EO_TUNE_CACHE");
@@ -1147,15 +894,20 @@ int set_mrhs_shape(int nr, int sites, int persist, int bz, int split) {
     return 0;
 }
 
+// The shape where nothing can be timed: links staged in LDS for as many
+// wavefronts as right-hand sides, up to 6.
+static MrhsCfg untuned_shape(const HopLaunch& h) { return {kNrLw, h.nrhs < 5 ? h.nrhs : 6, 0, 0, 0}; }
+
 hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
-    if (h.nrhs == 1) return launch_hop_single(h, s);
+    if (h.nrhs == 1) return run_single(h, s);
     MrhsCfg forced;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         forced = g_forced;
     }
-    if (forced.nr == 1) return launch_hop_single(h, s);
-    if (h.dmode && forced.nr != 0 && forced.nr != kNrLw) return launch_hop_single(h, s);   // no fused dot there
+    if (forced.nr == 1) return run_single(h, s);
+    // no fused dot and no clover blocks in the forms that hold links in registers
+    if ((h.dmode || h.clv) && forced.nr != 0 && forced.nr != kNrLw) return run_single(h, s);
     if (forced.nr == kNrLw) {
         MrhsCfg c = forced;
         if (c.s > lw_max_waves(h.fmt)) c.s = lw_max_waves(h.fmt);      // the format's most wavefronts
@@ -1163,9 +915,9 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
     }
     if (forced.nr < 0) {
         if (!lr_supported(h.fmt)) return launch_hop_single(h, s);
-        if ((forced.nr == -2 || forced.nr == -4) && !lr16_supported(h.fmt)) {
+        if ((forced.nr == -2 || forced.nr == -4) && (!lr16_supported(h.fmt) || h.fp32)) {
             MrhsCfg c = forced;
-            c.nr = forced.nr == -4 ? -3 : -1;          // FP32 arithmetic for the other formats
+            c.nr = forced.nr == -4 ? -3 : -1;          // FP32 arithmetic
             return launch_hop_mrhs(h, c, s);
         }
         return launch_hop_mrhs(h, forced, s);
@@ -1178,7 +930,7 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
         return c.nr <= 1 ? launch_hop_single(h, s) : launch_hop_mrhs(h, c, s);
     }
     const int epi = (h.y != nullptr ? 1 : 0) + (h.partial != nullptr ? 2 : 0) + (h.z != nullptr ? 4 : 0) +
-                    (h.dmode != 0 ? 8 : 0);
+                    (h.dmode != 0 ? 8 : 0) + (h.clv ? 16 : 0) + (h.fp32 ? 32 : 0);
     const TuneKey key{h.g.lx, h.g.ly, h.g.lz, h.g.lt, h.fmt, h.nrhs, epi};
     TuneEntry e;
     bool have = false;
@@ -1192,7 +944,7 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
         // each would add to the previous result.  Run it untuned.
         const size_t fb = (size_t)h.nrhs * spinor_field_bytes(h.g, h.fmt);
         const uintptr_t y = reinterpret_cast<uintptr_t>(h.y), o = reinterpret_cast<uintptr_t>(h.out);
-        if (y < o + fb && o < y + fb) return launch_hop_single(h, s);
+        if (y < o + fb && o < y + fb) return run_single(h, s);
     }
     if (!have && tuning_enabled()) {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1204,12 +956,18 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
             have = true;
         }
     }
+    if (!have && tuning_enabled()) {
+        // a stream under capture cannot be timed: record an untuned launch
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+            return run_cfg(h, untuned_shape(h), s);
+    }
     if (!have) {
         if (tuning_enabled()) {
             const hipError_t err = tune(h, s, &e);
             if (err != hipSuccess) return err;
         } else {
-            e.cfg = {h.nrhs >= 3 ? 3 : h.nrhs, 64, 0, 0, 0};
+            e.cfg = h.clv ? untuned_shape(h) : MrhsCfg{h.nrhs >= 3 ? 3 : h.nrhs, 64, 0, 0, 0};
             e.us = 0.f;
         }
         std::lock_guard<std::mutex> lk(g_tune_mu);

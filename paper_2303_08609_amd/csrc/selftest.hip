@@ -65,29 +65,35 @@ static int check_remap() {
     return 0;
 }
 
-// Every site is visited exactly once under each workgroup schedule.
+// Every site is visited exactly once under each workgroup schedule, and where
+// norm partials are written every 64-site chunk by one wavefront.
 static int check_sched(const int dims[4]) {
     const Geom g = make_geom(dims);
     for (uint32_t S : {64u, 128u, 256u}) {
-        for (int bz : {0, 2, 4, 8, -1, -2, -4, -8, -16}) {
-            const Sched sc = make_sched(g, bz, S);
-            if (bz && sc.bz == 0) continue;
-            const uint32_t nblk = (g.vh + S - 1) / S;
-            std::vector<char> seen(g.vh, 0);
-            for (uint32_t b = 0; b < nblk; ++b) {
-                const uint32_t f = block_first_site(sc, g, b, S);
-                for (uint32_t t = 0; t < S; ++t) {
-                    const uint32_t ih = f + t;
-                    if (ih >= g.vh) {
-                        if (sc.bz) return 31;     // blocked schedules have no ragged tail
-                        continue;
+        for (int bz : {0, 1, 2, 3, 4, 8, -1, -2, -4, -8, -16}) {
+            for (bool aligned : {false, true}) {
+                const Sched sc = make_sched(g, bz, S, aligned);
+                if (bz && sc.bz == 0) continue;
+                std::vector<char> seen(g.vh, 0), chunk((g.vh + 63) / 64, 0);
+                for (uint32_t b = 0; b < sc.nblk; ++b) {
+                    const SiteSpan sp = block_span(sc, g, b, S);
+                    if (sp.end > g.vh) return 31;
+                    for (uint32_t t = 0; t < S; ++t) {
+                        const uint32_t ih = sp.base + t;
+                        if (ih >= sp.end) continue;
+                        if (seen[ih]) return 30;
+                        seen[ih] = 1;
+                        if (aligned && t % 64 == 0) {
+                            if (ih % 64 || chunk[ih / 64]) return 33;
+                            chunk[ih / 64] = 1;
+                        }
                     }
-                    if (seen[ih]) return 30;
-                    seen[ih] = 1;
                 }
+                for (uint32_t i = 0; i < g.vh; ++i)
+                    if (!seen[i]) return 32;
+                for (size_t i = 0; aligned && i < chunk.size(); ++i)
+                    if (!chunk[i]) return 34;
             }
-            for (uint32_t i = 0; i < g.vh; ++i)
-                if (!seen[i]) return 32;
         }
     }
     return 0;

@@ -51,30 +51,40 @@ inline Geom make_geom(const int dims[4]) {
     return g;
 }
 
-// Schedule descriptor for block_first_site (weo_device.h); bz = 0 when the
+// Schedule descriptor for block_span (weo_device.h); bz = 0 when the
 // requested strip height does not fit the lattice or the workgroup size.
 struct SchedHost {
     int bz;             // 0: lexicographic; > 0: z strips; < 0: half-plane columns
+    uint32_t nblk;      // workgroups of the whole lattice
     uint32_t plane;
-    FastDiv d_bpp;      // blocks per plane (strips) or per half plane (columns)
+    uint32_t strip;     // sites of one strip in one t slice (strips)
+    FastDiv d_bpp;      // blocks per strip and t slice (strips) or per half plane (columns)
     FastDiv d_bz, d_lt;
     FastDiv d_nzb;      // strips of |bz| planes along z (columns)
 };
 
-// bz > 0 needs plane % S == 0, bz < 0 plane % (2 S) == 0; both need
-// lz % |bz| == 0.  Otherwise the schedule is lexicographic (bz = 0).
-inline SchedHost make_sched(const Geom& g, int bz, uint32_t sites_per_block) {
+// bz > 0: strips of bz planes along z, any lattice with lz > bz; the last
+// strip may be lower and the last workgroup of a strip in a t slice partly
+// filled.  With aligned (launches that write one norm partial per 64 sites)
+// every workgroup has to start on a multiple of 64 sites.  bz < 0 needs
+// plane % (2 S) == 0 and lz % |bz| == 0.  Otherwise the schedule is
+// lexicographic (bz = 0).
+inline SchedHost make_sched(const Geom& g, int bz, uint32_t sites_per_block, bool aligned = false) {
     SchedHost s;
     s.plane = (uint32_t)g.lxh * (uint32_t)g.ly;
     s.bz = 0;
     const uint32_t S = sites_per_block;
     const int az = bz < 0 ? -bz : bz;
-    const uint32_t parts = bz < 0 ? 2u : 1u;
-    if (bz != 0 && S > 0 && s.plane % (parts * S) == 0 && g.lz % az == 0) s.bz = bz;
-    s.d_bpp = make_fastdiv(s.bz ? s.plane / (parts * S) : 1);
+    if (S > 0 && bz > 0 && bz < g.lz && (!aligned || (bz * s.plane % 64 == 0 && g.st % 64 == 0))) s.bz = bz;
+    if (S > 0 && bz < 0 && s.plane % (2 * S) == 0 && g.lz % az == 0) s.bz = bz;
+    s.strip = s.bz > 0 ? (uint32_t)bz * s.plane : 0;
+    const uint32_t bpp = s.bz > 0 ? (s.strip + S - 1) / S : (s.bz < 0 ? s.plane / (2 * S) : 1);
+    const uint32_t nz = s.bz ? (uint32_t)((g.lz + az - 1) / az) : 1;
+    s.nblk = s.bz > 0 ? bpp * (uint32_t)g.lt * nz : (g.vh + S - 1) / S;
+    s.d_bpp = make_fastdiv(bpp);
     s.d_bz = make_fastdiv(s.bz ? (uint32_t)az : 1);
     s.d_lt = make_fastdiv((uint32_t)g.lt);
-    s.d_nzb = make_fastdiv(s.bz ? (uint32_t)(g.lz / az) : 1);
+    s.d_nzb = make_fastdiv(nz);
     return s;
 }
 

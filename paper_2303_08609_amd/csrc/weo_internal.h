@@ -53,6 +53,10 @@ struct HopLaunch {
     const void* dw = nullptr;
     double* pdre = nullptr;
     double* pdim = nullptr;
+    // packed site blocks of the whole clover field: the hop's result is
+    // multiplied by the output parity's blocks before the epilogue
+    const void* clv = nullptr;
+    bool fp32 = false;    // FP32 arithmetic for FP16 fields too (no packed FP16 kernels)
 };
 
 struct TuneCfg {
@@ -64,6 +68,7 @@ TuneCfg& hop_tune();                       // current single-rhs launch shape
 uint32_t hop_partials(const Geom& g);      // norm partials per rhs: one per 64 sites
 hipError_t launch_hop(const HopLaunch& h, hipStream_t s);          // picks the kernel
 hipError_t launch_hop_single(const HopLaunch& h, hipStream_t s);   // one lane per site
+hipError_t launch_hop_clover_single(const HopLaunch& h, hipStream_t s);   // the same with h.clv
 // Multi-rhs kernel: one lane per (site, group of nr rhs); links are loaded
 // once per lane and applied to its nr right-hand sides.  s = sites per
 // workgroup (64, 128 or 256), up to 256 / s rhs groups per workgroup and the
@@ -257,9 +262,6 @@ hipError_t launch_pack_clover(const Geom& g, int fmt, const void* canon, int can
 // out = y + alpha C_parity in  (y == nullptr: out = C_parity in)
 hipError_t launch_clover_site(const Geom& g, int fmt, int parity, const void* clv, const void* in, const void* y,
                               double alpha, void* out, int nrhs, hipStream_t s);
-// hop whose result is multiplied by the output parity's blocks before the
-// axpy / norm epilogue (one lane per site, nrhs grid rows)
-hipError_t launch_hop_clover(const HopLaunch& h, const void* clv, hipStream_t s);
 // M = 1 - kappa^2 C_e H_eo C_o H_oe or its adjoint (C: packed inverse blocks)
 hipError_t launch_apply_clover(const Geom& g, int fmt, const double phase[4][2], double kappa, int dagger,
                                const void* u, const void* clv, const void* in, void* out, void* tmp, int nrhs,
