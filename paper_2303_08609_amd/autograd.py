@@ -43,12 +43,15 @@ def _canon_prec(t):
     return W.WEO_F64 if t.dtype == torch.complex128 else W.WEO_F32
 
 
-def _link_grad_into(lat, fmt, u_packed, eta_p, psi_p, coeff, out, accumulate, project=False):
+def _link_grad_into(lat, fmt, u_packed, eta_p, psi_p, coeff, out, accumulate, project=False, lam_o=None, r_o=None):
     """out (+)= link gradient of coeff * Re<Lambda, H R> with
     Lambda = (eta, H_eo^dag eta), R = (psi, H_oe psi); with project, the
-    su(3) force TH(i U g^dag) instead."""
-    lam_o = lat.hop(u_packed, eta_p, fmt, out_parity=1, dagger=True)
-    r_o = lat.hop(u_packed, psi_p, fmt, out_parity=1, dagger=False)
+    su(3) force TH(i U g^dag) instead.  lam_o, r_o: the odd halves where an
+    operator apply has left them in its scratch field."""
+    if lam_o is None:
+        lam_o = lat.hop(u_packed, eta_p, fmt, out_parity=1, dagger=True)
+    if r_o is None:
+        r_o = lat.hop(u_packed, psi_p, fmt, out_parity=1, dagger=False)
     flags = (W.WEO_FORCE_ACCUMULATE if accumulate else 0) | (W.WEO_FORCE_PROJECT if project else 0)
     W.check(W.wilson_eo_force(lat.c, fmt.c, _ptr(u_packed), _ptr(eta_p), _ptr(lam_o), _ptr(psi_p),
                               _ptr(r_o), float(coeff), flags, _ptr(out), _canon_prec(out),
@@ -56,33 +59,38 @@ def _link_grad_into(lat, fmt, u_packed, eta_p, psi_p, coeff, out, accumulate, pr
 
 
 class WilsonApply(torch.autograd.Function):
+    """The packed links, and for a link gradient the packed psi and H_oe psi
+    (the odd half the apply computes on its way), are saved for backward:
+    packing them and hopping again took a quarter of a backward pass."""
+
     @staticmethod
     def forward(ctx, u, psi, lat: Lattice, dagger: bool = False):
         fmt = _fmt_for(psi)
         u_p = lat.pack_gauge(u.contiguous(), fmt)
         x_p = lat.pack_spinor(psi.contiguous(), fmt)
-        out_p = lat.apply(u_p, x_p, fmt, dagger=dagger)
-        ctx.save_for_backward(u, psi)
+        odd = lat.new_spinor(fmt)
+        out_p = lat.apply(u_p, x_p, fmt, dagger=dagger, tmp=odd)
+        keep = (x_p, odd) if ctx.needs_input_grad[0] and not dagger else ()
+        ctx.save_for_backward(u, psi, u_p, *keep)
         ctx.lat, ctx.fmt, ctx.dagger = lat, fmt, dagger
         return lat.unpack_spinor(out_p, fmt, dtype=psi.dtype)
 
     @staticmethod
     def backward(ctx, g_out):
-        u, psi = ctx.saved_tensors
+        u, psi, u_p, *keep = ctx.saved_tensors
         lat, fmt, dagger = ctx.lat, ctx.fmt, ctx.dagger
-        g_out = g_out.contiguous()
-        u_p = lat.pack_gauge(u.contiguous(), fmt)
-        g_p = lat.pack_spinor(g_out, fmt)
-        g_u = g_psi = None
+        g_p = lat.pack_spinor(g_out.contiguous(), fmt)
+        g_u = g_psi = lam_o = None
         if ctx.needs_input_grad[1]:
-            g_psi = lat.unpack_spinor(lat.apply(u_p, g_p, fmt, dagger=not dagger), fmt,
+            lam_o = lat.new_spinor(fmt)         # H_oe^dag g_out once the adjoint has run
+            g_psi = lat.unpack_spinor(lat.apply(u_p, g_p, fmt, dagger=not dagger, tmp=lam_o), fmt,
                                       dtype=psi.dtype)
         if ctx.needs_input_grad[0]:
             if dagger:
                 raise NotImplementedError("link gradient of M^dag is not provided")
-            x_p = lat.pack_spinor(psi.contiguous(), fmt)
+            x_p, r_o = keep
             g_u = torch.empty(lat.gauge_shape(), dtype=u.dtype, device=u.device)
-            _link_grad_into(lat, fmt, u_p, g_p, x_p, -lat.kappa ** 2, g_u, False)
+            _link_grad_into(lat, fmt, u_p, g_p, x_p, -lat.kappa ** 2, g_u, False, lam_o=lam_o, r_o=r_o)
         return g_u, g_psi, None, None
 
 
@@ -108,13 +116,14 @@ class WilsonSolve(torch.autograd.Function):
             u_p = lat.pack_gauge(u.contiguous(), fmt)
             lam_p = lat.pack_spinor(lam, fmt)
             chi_p = lat.pack_spinor(chi.contiguous(), fmt)
-            m_lam = lat.apply(u_p, lam_p, fmt)
-            m_chi = lat.apply(u_p, chi_p, fmt)
+            lam_h, chi_h = lat.new_spinor(fmt), lat.new_spinor(fmt)     # H_oe lambda, H_oe chi
+            m_lam = lat.apply(u_p, lam_p, fmt, tmp=lam_h)
+            m_chi = lat.apply(u_p, chi_p, fmt, tmp=chi_h)
             g_u = torch.empty(lat.gauge_shape(), dtype=u.dtype, device=u.device)
             # dL = -Re<M lam, dM chi> - Re<M chi, dM lam> with dM = -kappa^2 d(H_eo H_oe):
             # two bilinear terms, each with coefficient +kappa^2
-            _link_grad_into(lat, fmt, u_p, m_lam, chi_p, lat.kappa ** 2, g_u, False)
-            _link_grad_into(lat, fmt, u_p, m_chi, lam_p, lat.kappa ** 2, g_u, True)
+            _link_grad_into(lat, fmt, u_p, m_lam, chi_p, lat.kappa ** 2, g_u, False, r_o=chi_h)
+            _link_grad_into(lat, fmt, u_p, m_chi, lam_p, lat.kappa ** 2, g_u, True, r_o=lam_h)
         return g_u, g_phi, None, None, None
 
 

@@ -16,7 +16,8 @@ LINK = {18: W.WEO_LINK18, 12: W.WEO_LINK12}
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the handle alone: building torch's Stream object costs as much as a launch
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: torch.Tensor | None):
