@@ -51,24 +51,20 @@ __device__ __forceinline__ void load_block(const uint8_t* base, uint32_t n, uint
     }
 }
 
-// v <- A v from the two block records already in registers.
-template <int CP, class C, class RR>
-__device__ __forceinline__ void clover_apply_raw(const RR& r0, const RR& r1, C* v) {
+// v <- A v, the two blocks as records whose unpack gives the arithmetic type.
+template <class C, class B>
+__device__ __forceinline__ void clover_apply_blocks(const B& r0, const B& r1, C* v) {
     using R = decltype(C().x);
-    using CR = typename St<CP>::real;
     C a[6], b[6], ya[6], yb[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) { a[k] = add(v[k], v[6 + k]); b[k] = sub(v[k], v[6 + k]); }
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        cx<CR> w[kCloverSlots];
-        (q == 0 ? r0 : r1).unpack(w);
         C blk[kCloverSlots];
-#pragma unroll
-        for (int k = 0; k < kCloverSlots; ++k) { blk[k].x = (R)w[k].x; blk[k].y = (R)w[k].y; }
+        (q == 0 ? r0 : r1).unpack(blk);
         herm6_mul(blk, q == 0 ? a : b, q == 0 ? ya : yb);
     }
-    const R h = R(0.5);
+    const R h = R(0.5);     // the two 1/sqrt2 of the basis change
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         v[k].x = h * (ya[k].x + yb[k].x);
@@ -76,6 +72,32 @@ __device__ __forceinline__ void clover_apply_raw(const RR& r0, const RR& r1, C* 
         v[6 + k].x = h * (ya[k].x - yb[k].x);
         v[6 + k].y = h * (ya[k].y - yb[k].y);
     }
+}
+
+// Blocks in LDS, [slot][64 sites], as staged by a workgroup of 64 sites.
+template <class C> struct BlockInLds {
+    const C (*w)[64];
+    uint32_t lane;
+    __device__ __forceinline__ void unpack(C* v) const {
+#pragma unroll
+        for (int k = 0; k < kCloverSlots; ++k) v[k] = w[k][lane];
+    }
+};
+
+// v <- A v from the two block records already in registers.
+template <int CP, class C, class RR> struct WidenedBlock {
+    const RR& r;
+    __device__ __forceinline__ void unpack(C* v) const {
+        cx<typename St<CP>::real> w[kCloverSlots];
+        r.unpack(w);
+#pragma unroll
+        for (int k = 0; k < kCloverSlots; ++k) v[k] = mk<C>(w[k].x, w[k].y);
+    }
+};
+template <int CP, class C, class RR>
+__device__ __forceinline__ void clover_apply_raw(const RR& r0, const RR& r1, C* v) {
+    const WidenedBlock<CP, C, RR> b0{r0}, b1{r1};
+    clover_apply_blocks(b0, b1, v);
 }
 
 // v <- A v for the site matrix A of half-index i; par_base points at the

@@ -132,6 +132,7 @@ hipError_t launch_hop_single(const HopLaunch& h, hipStream_t s) {
     P.spinor_bytes = spinor_field_bytes(h.g, h.fmt);
     P.link_block = gauge_block_bytes(h.g, h.fmt);
     P.sched = make_sched(h.g, g_hop_tune.bz, (uint32_t)g_hop_tune.block, h.partial != nullptr);
+    if (hop_is_small(h)) return launch_hop_small(h, P, s);
     const dim3 block(g_hop_tune.block);
     const dim3 grid(P.sched.nblk, h.nrhs);
     switch (h.fmt) {

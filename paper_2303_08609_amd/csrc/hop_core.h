@@ -118,6 +118,12 @@ struct HopParams {
     Sched sched;            // workgroup -> sites order
 };
 
+// The kernel for lattices that leave the chip idle (hop_small.hip, with the
+// timings that set the limit on sites times right-hand sides).
+constexpr uint64_t kHopSmallSites = 1u << 15;
+bool hop_is_small(const HopLaunch& h);
+hipError_t launch_hop_small(const HopLaunch& h, const HopParams& P, hipStream_t s);
+
 // Epilogue of a hop with addends: acc = alpha acc + cy y (+ z) for rhs r at
 // site ih (cy = 1 rounds exactly as a plain axpy).
 template <int SP, class C>

@@ -106,30 +106,6 @@ __device__ __forceinline__ void lw_stage_block(const MrhsParams& M, int q, uint3
     for (int e = 0; e < kCloverSlots; ++e) cb[q][e][lane] = w[e];
 }
 
-// v <- A v from the staged blocks.
-template <class C>
-__device__ __forceinline__ void lw_clover(const C (*cb)[kCloverSlots][64], uint32_t lane, C* v) {
-    using R = decltype(C().x);
-    C a[6], b[6], ya[6], yb[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) { a[k] = add(v[k], v[6 + k]); b[k] = sub(v[k], v[6 + k]); }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        C w[kCloverSlots];
-#pragma unroll
-        for (int e = 0; e < kCloverSlots; ++e) w[e] = cb[q][e][lane];
-        herm6_mul(w, q == 0 ? a : b, q == 0 ? ya : yb);
-    }
-    const R h = R(0.5);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        v[k].x = h * (ya[k].x + yb[k].x);
-        v[k].y = h * (ya[k].y + yb[k].y);
-        v[6 + k].x = h * (ya[k].x - yb[k].x);
-        v[6 + k].y = h * (ya[k].y - yb[k].y);
-    }
-}
-
 // Most wavefronts per workgroup.
 template <int SP> constexpr int lw_maxw() { return SP == P_F64 ? 8 : 12; }
 // Wavefronts per SIMD asked for.
@@ -205,7 +181,10 @@ __global__ void __launch_bounds__(64 * lw_maxw<SP>(), (lw_waves<SP, DOT>())) k_h
 #pragma unroll
             for (int k = 0; k < 12; ++k) acc[k] = czero<C>();
             lw_step<SP, DAG, 0>(P, lds.lk, lo, in, in_next, no, ring, acc);
-            if constexpr (CLV) lw_clover(lds.cb, lo, acc);
+            if constexpr (CLV) {
+                const BlockInLds<C> b0{lds.cb[0], lo}, b1{lds.cb[1], lo};
+                clover_apply_blocks(b0, b1, acc);
+            }
             if (P.y) hop_addends<SP>(P, (size_t)r, ih, acc);
             store_rec<SP, 12, C, mrhs_nt_store<SP>()>(P.out + (size_t)r * P.spinor_bytes, n, ih, acc);
             if (P.partial) hop_reduce<SP, DOT>(P, (size_t)r, ih, acc, nrm, dre, dim);
