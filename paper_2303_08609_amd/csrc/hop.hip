@@ -11,7 +11,7 @@ namespace weo {
 template <int SP> struct Waves { static constexpr int n = WEO_WAVES_F32; };
 template <> struct Waves<P_F64> { static constexpr int n = WEO_WAVES_F64; };
 
-template <int SP, int LP, bool L12, bool DAG, bool AXPY, bool NORM, bool CPH, bool DOT = false>
+template <int SP, int LP, bool L12, bool DAG, bool AXPY, bool NORM, int CPH, bool DOT = false>
 __global__ void __launch_bounds__(256, Waves<SP>::n > 0 ? Waves<SP>::n : 1) k_hop(const HopParams P) {
     using R = typename Arith<SP>::R;
     using C = cx<R>;
@@ -79,15 +79,14 @@ template <int SP, int LP, bool L12>
 static hipError_t launch_fmt(const HopLaunch& h, const HopParams& P, dim3 grid, dim3 block,
                              hipStream_t s) {
     const bool axpy = h.y != nullptr, norm = h.partial != nullptr;
-    bool cph = false;
-    for (int m = 0; m < 4; ++m) cph = cph || h.phase[m][1] != 0.0;
+    const int pm = phase_mode(h.phase);
     if (h.dmode) {
         // the fused dot: an M epilogue (axpy and norm) only
         if (!axpy || !norm) return hipErrorInvalidValue;
 #define WEO_HOP_DOT(D)                                                                                   \
         if (h.dagger == D) {                                                                             \
-            if (cph) hipLaunchKernelGGL((k_hop<SP, LP, L12, D, true, true, true, true>), grid, block, 0, s, P);   \
-            else hipLaunchKernelGGL((k_hop<SP, LP, L12, D, true, true, false, true>), grid, block, 0, s, P);  \
+            if (pm == PH_CPLX) hipLaunchKernelGGL((k_hop<SP, LP, L12, D, true, true, PH_CPLX, true>), grid, block, 0, s, P); \
+            else hipLaunchKernelGGL((k_hop<SP, LP, L12, D, true, true, PH_REAL, true>), grid, block, 0, s, P);  \
             return hipGetLastError();                                                                    \
         }
         WEO_HOP_DOT(0) WEO_HOP_DOT(1)
@@ -96,10 +95,12 @@ static hipError_t launch_fmt(const HopLaunch& h, const HopParams& P, dim3 grid, 
     }
 #define WEO_HOP_CASE(D, A, N)                                                            \
     if (h.dagger == D && axpy == A && norm == N) {                                       \
-        if (cph)                                                                          \
-            hipLaunchKernelGGL((k_hop<SP, LP, L12, D, A, N, true>), grid, block, 0, s, P);  \
+        if (pm == PH_REAL_T)                                                              \
+            hipLaunchKernelGGL((k_hop<SP, LP, L12, D, A, N, PH_REAL_T>), grid, block, 0, s, P); \
+        else if (pm == PH_REAL)                                                           \
+            hipLaunchKernelGGL((k_hop<SP, LP, L12, D, A, N, PH_REAL>), grid, block, 0, s, P); \
         else                                                                              \
-            hipLaunchKernelGGL((k_hop<SP, LP, L12, D, A, N, false>), grid, block, 0, s, P); \
+            hipLaunchKernelGGL((k_hop<SP, LP, L12, D, A, N, PH_CPLX>), grid, block, 0, s, P); \
         return hipGetLastError();                                                         \
     }
     WEO_HOP_CASE(0, false, false) WEO_HOP_CASE(1, false, false)

@@ -25,7 +25,7 @@ struct CloverHopParams {
 // The neighbour pipeline of the plain hop, with the two block records of the
 // site loaded in the steps whose ring slot is no longer needed (the last D
 // directions), so their latency hides behind the last directions' arithmetic.
-template <int SP, int LP, bool L12, bool DAG, bool CPH, int D, int K, class C>
+template <int SP, int LP, bool L12, bool DAG, int CPH, int D, int K, class C>
 __device__ __forceinline__ void clv_step(const CloverHopParams& Q, const uint8_t* in, const Nbr& nb, uint32_t ih,
                                          NbrRaw<SP, LP, L12> (&ring)[D + 1], RawRec<LP, kCloverSlots> (&cb)[2],
                                          C* acc) {
@@ -44,7 +44,7 @@ __device__ __forceinline__ void clv_step(const CloverHopParams& Q, const uint8_t
     if constexpr (K + 1 < 8) clv_step<SP, LP, L12, DAG, CPH, D, K + 1>(Q, in, nb, ih, ring, cb, acc);
 }
 
-template <int SP, int LP, bool L12, bool DAG, bool AXPY, bool NORM, bool CPH>
+template <int SP, int LP, bool L12, bool DAG, bool AXPY, bool NORM, int CPH>
 __global__ void __launch_bounds__(256) k_hop_clv(const CloverHopParams Q) {
     using R = typename Arith<SP>::R;
     using C = cx<R>;
@@ -116,12 +116,12 @@ __global__ void __launch_bounds__(256) k_hop_clv(const CloverHopParams Q) {
 template <int SP, int LP, bool L12>
 static hipError_t clv_fmt(const HopLaunch& h, const CloverHopParams& Q, dim3 grid, dim3 block, hipStream_t s) {
     const bool axpy = h.y != nullptr, norm = h.partial != nullptr;
-    bool cph = false;
-    for (int m = 0; m < 4; ++m) cph = cph || h.phase[m][1] != 0.0;
+    const int pm = phase_mode(h.phase);
 #define WEO_CLV(D, A, N)                                                                       \
     if (h.dagger == D && axpy == A && norm == N) {                                             \
-        if (cph) hipLaunchKernelGGL((k_hop_clv<SP, LP, L12, D, A, N, true>), grid, block, 0, s, Q);  \
-        else hipLaunchKernelGGL((k_hop_clv<SP, LP, L12, D, A, N, false>), grid, block, 0, s, Q);     \
+        if (pm == PH_REAL_T) hipLaunchKernelGGL((k_hop_clv<SP, LP, L12, D, A, N, PH_REAL_T>), grid, block, 0, s, Q); \
+        else if (pm == PH_REAL) hipLaunchKernelGGL((k_hop_clv<SP, LP, L12, D, A, N, PH_REAL>), grid, block, 0, s, Q); \
+        else hipLaunchKernelGGL((k_hop_clv<SP, LP, L12, D, A, N, PH_CPLX>), grid, block, 0, s, Q);   \
         return hipGetLastError();                                                              \
     }
     WEO_CLV(0, false, false) WEO_CLV(1, false, false)

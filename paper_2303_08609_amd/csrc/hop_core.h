@@ -21,6 +21,7 @@
 // record has exactly one writer.
 #pragma once
 
+#include "half_spinor.h"
 #include "weo_device.h"
 #include "weo_internal.h"
 
@@ -77,10 +78,10 @@ template <int SP> constexpr bool hop_nt_store() { return HopShape<SP>::nt_store;
 #define WEO_WAVES_F64 0
 #endif
 
-// FP16 values of the 12-real formats are converted to FP32 where they are
+// FP16 links of the 12-real formats are converted to FP32 where they are
 // unpacked (an empty asm pins the converted values).  Left alone, the
 // compiler folds the conversions into mixed-precision FMAs and keeps the raw
-// words live longer: FP16/FP16/12 then needs 150 VGPRs instead of 114
+// words live longer: FP16/FP16/12 then needs 150 VGPRs instead of 101
 // (3 instead of 4 waves per SIMD) and its hop runs 8 % slower.  The 18-real
 // formats measured no gain from it.
 template <int SP, int LP, bool L12> constexpr bool hop_pin_f16() { return L12; }
@@ -195,15 +196,26 @@ __device__ __forceinline__ void hop_partials_out(const HopParams& P, size_t r, u
     }
 }
 
-// Link U as 9 complex numbers (row-major); a 12-real record is completed with
-// row 2 = conj(row0 x row1), exact for det U = 1.
+// conj(a b - c d), 8 fused operations.
+template <class C> __device__ __forceinline__ C cross_conj(C a, C b, C c, C d) {
+    C r;
+    r.x = fma(c.y, d.y, fma(-c.x, d.x, fma(-a.y, b.y, a.x * b.x)));
+    r.y = fma(c.y, d.x, fma(c.x, d.y, fma(-a.y, b.x, -a.x * b.y)));
+    return r;
+}
+// Row 2 of a 12-real link, conj(row0 x row1), exact for det U = 1.
+template <class C> __device__ __forceinline__ void complete_link(C* u) {
+    u[6] = cross_conj(u[1], u[5], u[2], u[4]);
+    u[7] = cross_conj(u[2], u[3], u[0], u[5]);
+    u[8] = cross_conj(u[0], u[4], u[1], u[3]);
+}
+
+// Link U as 9 complex numbers (row-major); a 12-real record is completed.
 template <int LP, bool L12, bool NT = false, class C>
 __device__ __forceinline__ void load_link(const uint8_t* base, uint32_t n, uint32_t i, C* u) {
     if constexpr (L12) {
         load_rec<LP, 6, NT>(base, n, i, u);
-        u[6] = conj_(sub(mul(u[1], u[5]), mul(u[2], u[4])));
-        u[7] = conj_(sub(mul(u[2], u[3]), mul(u[0], u[5])));
-        u[8] = conj_(sub(mul(u[0], u[4]), mul(u[1], u[3])));
+        complete_link(u);
     } else {
         load_rec<LP, 9, NT>(base, n, i, u);
     }
@@ -223,91 +235,115 @@ __device__ __forceinline__ void load_link_as(const uint8_t* base, uint32_t n, ui
     }
 }
 
-// One direction: project with (1 - S gamma_mu), boundary phase (complex when
-// CPH, else real), multiply by U (FWD) or U^dag (!FWD), reconstruct and
-// accumulate.
-template <int MU, int S, bool FWD, bool CPH, class C, bool APPLY_PHASE = true>
-__device__ __forceinline__ void hop_dir(const C* p, const C* u, bool edge, C phase, C* acc) {
-    C h0[3], h1[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const C p0 = p[c], p1 = p[3 + c], p2 = p[6 + c], p3 = p[9 + c];
-        if constexpr (MU == 0) {
-            h0[c] = S > 0 ? add(p0, imul(p3)) : sub(p0, imul(p3));
-            h1[c] = S > 0 ? add(p1, imul(p2)) : sub(p1, imul(p2));
-        } else if constexpr (MU == 1) {
-            h0[c] = S > 0 ? add(p0, p3) : sub(p0, p3);
-            h1[c] = S > 0 ? sub(p1, p2) : add(p1, p2);
-        } else if constexpr (MU == 2) {
-            h0[c] = S > 0 ? add(p0, imul(p2)) : sub(p0, imul(p2));
-            h1[c] = S > 0 ? sub(p1, imul(p3)) : add(p1, imul(p3));
-        } else {
-            h0[c] = S > 0 ? p2 : p0;
-            h1[c] = S > 0 ? p3 : p1;
-        }
+// Boundary phases a kernel is built for: any real ones, any complex ones, or
+// (the usual case) 1 in x, y and z and a real one in t, where the products
+// with the other directions' phases are left out.  The FP16/12 hop is bound
+// by its vector instructions and its traffic about equally; this, the FP16
+// projection (add_halves) and the fused third row (cross_conj) took it from
+// 1548 to 1386 vector instructions per site: apply at 48^3x96 706 -> 694 us,
+// clover apply of 12 FP16 fields of 16^3x32 75 -> 70 us.
+enum : int { PH_REAL = 0, PH_CPLX = 1, PH_REAL_T = 2 };
+
+inline int phase_mode(const double ph[4][2]) {
+    bool one = true;
+    for (int m = 0; m < 4; ++m) {
+        if (ph[m][1] != 0.0) return PH_CPLX;
+        if (m < 3 && ph[m][0] != 1.0) one = false;
     }
-    // Boundary phase: applied without a branch, so that the loads of the
-    // next neighbours can be scheduled ahead of this arithmetic.  (Callers
-    // that fold the phase into the link pass APPLY_PHASE = false.)
-    if constexpr (!APPLY_PHASE) {
-    } else if constexpr (CPH) {
+    return one ? PH_REAL_T : PH_REAL;
+}
+
+// One direction from its half spinor h: boundary phase, product with U (FWD)
+// or U^dag (!FWD), reconstruction and accumulation.  The phase is applied
+// without a branch, so that the loads of the next neighbours can be scheduled
+// ahead of this arithmetic.  (Callers that fold the phase into the link pass
+// APPLY_PHASE = false.)
+template <int MU, int S, bool FWD, int PH, bool APPLY_PHASE, class C>
+__device__ __forceinline__ void hop_half(C* h, const C* u, bool edge, C phase, C* acc) {
+    if constexpr (APPLY_PHASE && PH == PH_CPLX) {
         const C ph = edge ? phase : mk<C>(1, 0);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) { h0[c] = mul(ph, h0[c]); h1[c] = mul(ph, h1[c]); }
-    } else {
+        for (int e = 0; e < 6; ++e) h[e] = mul(ph, h[e]);
+    } else if constexpr (APPLY_PHASE && (PH == PH_REAL || MU == 3)) {
         const auto sg = edge ? phase.x : decltype(phase.x)(1);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) { h0[c] = scal(sg, h0[c]); h1[c] = scal(sg, h1[c]); }
+        for (int e = 0; e < 6; ++e) h[e] = scal(sg, h[e]);
     }
-    C g0[3], g1[3];
+    C g[6];
+    half_su3<FWD>(u, h, g);
+    half_rebuild<MU, S>(g, decltype(C().x)(1), acc);
+}
+
+// One direction: project with (1 - S gamma_mu), then hop_half.
+template <int MU, int S, bool FWD, int PH, class C, bool APPLY_PHASE = true>
+__device__ __forceinline__ void hop_dir(const C* p, const C* u, bool edge, C phase, C* acc) {
+    C h[6];
+    half_project<MU, S>(p, h);
+    hop_half<MU, S, FWD, PH, APPLY_PHASE>(h, u, edge, phase, acc);
+}
+
+// a + b or a - b of two FP16 halves (selected by AH, BH) of packed words, in
+// FP32: one instruction where converting both and adding takes three.
+template <bool AH, bool BH, bool NEG>
+__device__ __forceinline__ float add_halves(uint32_t a, uint32_t b) {
+    float r;
+#define WEO_MIX(ONE, SEL) asm("v_fma_mix_f32 %0, %1, " ONE ", %2 op_sel:" SEL " op_sel_hi:[1,0,1]" : "=v"(r) : "v"(b), "v"(a))
+    if constexpr (NEG) {
+        if constexpr (AH && BH) WEO_MIX("-1.0", "[1,0,1]");
+        else if constexpr (AH) WEO_MIX("-1.0", "[0,0,1]");
+        else if constexpr (BH) WEO_MIX("-1.0", "[1,0,0]");
+        else WEO_MIX("-1.0", "[0,0,0]");
+    } else {
+        if constexpr (AH && BH) WEO_MIX("1.0", "[1,0,1]");
+        else if constexpr (AH) WEO_MIX("1.0", "[0,0,1]");
+        else if constexpr (BH) WEO_MIX("1.0", "[1,0,0]");
+        else WEO_MIX("1.0", "[0,0,0]");
+    }
+#undef WEO_MIX
+    return r;
+}
+// a + i b (NEG: a - i b), a + b (a - b) of packed complex numbers
+template <bool NEG> __device__ __forceinline__ float2 add_i(uint32_t a, uint32_t b) {
+    return make_float2(add_halves<false, true, !NEG>(a, b), add_halves<true, false, NEG>(a, b));
+}
+template <bool NEG> __device__ __forceinline__ float2 add_1(uint32_t a, uint32_t b) {
+    return make_float2(add_halves<false, false, NEG>(a, b), add_halves<true, true, NEG>(a, b));
+}
+
+// half_project of a record as loaded: FP16 records without converting their
+// values first (x, y, z; the values are those of half_project, FP32 sums of
+// exact operands).
+template <int SP, int MU, int S, class C>
+__device__ __forceinline__ void project_raw(const RawRec<SP, 12>& r, C* h) {
+    if constexpr (SP == P_F16 && MU < 3) {
+        uint32_t p[12];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if constexpr (FWD) {
-            g0[a] = mul(u[3 * a], h0[0]);
-            g1[a] = mul(u[3 * a], h1[0]);
-            g0[a] = fma_(u[3 * a + 1], h0[1], g0[a]);
-            g1[a] = fma_(u[3 * a + 1], h1[1], g1[a]);
-            g0[a] = fma_(u[3 * a + 2], h0[2], g0[a]);
-            g1[a] = fma_(u[3 * a + 2], h1[2], g1[a]);
-        } else {
-            g0[a] = mulc(u[a], h0[0]);
-            g1[a] = mulc(u[a], h1[0]);
-            g0[a] = fmac_(u[3 + a], h0[1], g0[a]);
-            g1[a] = fmac_(u[3 + a], h1[1], g1[a]);
-            g0[a] = fmac_(u[6 + a], h0[2], g0[a]);
-            g1[a] = fmac_(u[6 + a], h1[2], g1[a]);
+        for (int q = 0; q < 3; ++q) {
+            p[4 * q] = r.w[q].x; p[4 * q + 1] = r.w[q].y; p[4 * q + 2] = r.w[q].z; p[4 * q + 3] = r.w[q].w;
         }
-    }
-    using R = decltype(C().x);
+        constexpr bool N = S < 0;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if constexpr (MU == 3) {
-            if constexpr (S > 0) {
-                acc[6 + a].x = fma(R(2), g0[a].x, acc[6 + a].x); acc[6 + a].y = fma(R(2), g0[a].y, acc[6 + a].y);
-                acc[9 + a].x = fma(R(2), g1[a].x, acc[9 + a].x); acc[9 + a].y = fma(R(2), g1[a].y, acc[9 + a].y);
+        for (int c = 0; c < 3; ++c) {
+            if constexpr (MU == 0) {
+                h[c] = add_i<N>(p[c], p[9 + c]);
+                h[3 + c] = add_i<N>(p[3 + c], p[6 + c]);
+            } else if constexpr (MU == 1) {
+                h[c] = add_1<N>(p[c], p[9 + c]);
+                h[3 + c] = add_1<!N>(p[3 + c], p[6 + c]);
             } else {
-                acc[a].x = fma(R(2), g0[a].x, acc[a].x); acc[a].y = fma(R(2), g0[a].y, acc[a].y);
-                acc[3 + a].x = fma(R(2), g1[a].x, acc[3 + a].x); acc[3 + a].y = fma(R(2), g1[a].y, acc[3 + a].y);
-            }
-        } else {
-            acc[a] = add(acc[a], g0[a]);
-            acc[3 + a] = add(acc[3 + a], g1[a]);
-            if constexpr (MU == 0) {          // lower = (-S i g1, -S i g0)
-                acc[6 + a] = S > 0 ? sub(acc[6 + a], imul(g1[a])) : add(acc[6 + a], imul(g1[a]));
-                acc[9 + a] = S > 0 ? sub(acc[9 + a], imul(g0[a])) : add(acc[9 + a], imul(g0[a]));
-            } else if constexpr (MU == 1) {   // lower = (-S g1, S g0)
-                acc[6 + a] = S > 0 ? sub(acc[6 + a], g1[a]) : add(acc[6 + a], g1[a]);
-                acc[9 + a] = S > 0 ? add(acc[9 + a], g0[a]) : sub(acc[9 + a], g0[a]);
-            } else {                          // lower = (-S i g0, S i g1)
-                acc[6 + a] = S > 0 ? sub(acc[6 + a], imul(g0[a])) : add(acc[6 + a], imul(g0[a]));
-                acc[9 + a] = S > 0 ? add(acc[9 + a], imul(g1[a])) : sub(acc[9 + a], imul(g1[a]));
+                h[c] = add_i<N>(p[c], p[6 + c]);
+                h[3 + c] = add_i<!N>(p[3 + c], p[9 + c]);
             }
         }
+    } else {
+        C p[12];
+        r.unpack(p);
+        half_project<MU, S>(p, h);
     }
 }
 
 // Both neighbours of direction MU for one rhs.
-template <int SP, int LP, bool L12, bool DAG, bool CPH, int MU, class C>
+template <int SP, int LP, bool L12, bool DAG, int CPH, int MU, class C>
 __device__ __forceinline__ void hop_mu(const HopParams& P, const uint8_t* in, const Nbr& nb,
                                        uint32_t ih, C* acc) {
     constexpr int SF = DAG ? -1 : 1;      // forward term: (1 - SF gamma)
@@ -351,15 +387,16 @@ __device__ __forceinline__ void issue(const HopParams& P, const uint8_t* in, con
     r.sp.load(in, n, nb.i[K]);
 }
 
-template <int SP, int LP, bool L12, bool DAG, bool CPH, int K, class C>
+template <int SP, int LP, bool L12, bool DAG, int CPH, int K, class C>
 __device__ __forceinline__ void consume(const HopParams& P, const Nbr& nb, const NbrRaw<SP, LP, L12>& r,
                                         C* acc) {
     constexpr int MU = K / 2;
     constexpr int SF = DAG ? -1 : 1;
     using R = decltype(C().x);
-    C p[12], u[9];
-    r.sp.unpack(p);
-    if constexpr (hop_pin_f16<SP, LP, L12>() && SP == P_F16) pin_values(p, 12);
+    constexpr bool FWD = (K & 1) == 0;
+    constexpr int S = FWD ? SF : -SF;
+    C h[6], u[9];
+    project_raw<SP, MU, S>(r.sp, h);
     {
         using LR = typename St<LP>::real;
         cx<LR> w[9];
@@ -367,20 +404,16 @@ __device__ __forceinline__ void consume(const HopParams& P, const Nbr& nb, const
         if constexpr (hop_pin_f16<SP, LP, L12>() && LP == P_F16) pin_values(w, L12 ? 6 : 9);
 #pragma unroll
         for (int k = 0; k < (L12 ? 6 : 9); ++k) { u[k].x = (R)w[k].x; u[k].y = (R)w[k].y; }
-        if constexpr (L12) {
-            u[6] = conj_(sub(mul(u[1], u[5]), mul(u[2], u[4])));
-            u[7] = conj_(sub(mul(u[2], u[3]), mul(u[0], u[5])));
-            u[8] = conj_(sub(mul(u[0], u[4]), mul(u[1], u[3])));
-        }
+        if constexpr (L12) complete_link(u);
     }
     C phase;
     phase.x = (R)P.ph[MU][0];
     phase.y = (R)P.ph[MU][1];
-    if constexpr ((K & 1) == 0) hop_dir<MU, SF, true, CPH>(p, u, nb.edge[K], phase, acc);
-    else hop_dir<MU, -SF, false, CPH>(p, u, nb.edge[K], conj_(phase), acc);
+    if constexpr (!FWD) phase = conj_(phase);
+    hop_half<MU, S, FWD, CPH, true>(h, u, nb.edge[K], phase, acc);
 }
 
-template <int SP, int LP, bool L12, bool DAG, bool CPH, int D, int K, class C>
+template <int SP, int LP, bool L12, bool DAG, int CPH, int D, int K, class C>
 __device__ __forceinline__ void pipe_step(const HopParams& P, const uint8_t* in, const Nbr& nb, uint32_t ih,
                                           NbrRaw<SP, LP, L12> (&ring)[D + 1], C* acc) {
     if constexpr (K + D < 8) issue<SP, LP, L12, K + D>(P, in, nb, ih, ring[(K + D) % (D + 1)]);
@@ -390,7 +423,7 @@ __device__ __forceinline__ void pipe_step(const HopParams& P, const uint8_t* in,
     if constexpr (K + 1 < 8) pipe_step<SP, LP, L12, DAG, CPH, D, K + 1>(P, in, nb, ih, ring, acc);
 }
 
-template <int SP, int LP, bool L12, bool DAG, bool CPH, int D, int K = 0>
+template <int SP, int LP, bool L12, bool DAG, int CPH, int D, int K = 0>
 __device__ __forceinline__ void pipe_prologue(const HopParams& P, const uint8_t* in, const Nbr& nb, uint32_t ih,
                                               NbrRaw<SP, LP, L12> (&ring)[D + 1]) {
     if constexpr (K < D) {

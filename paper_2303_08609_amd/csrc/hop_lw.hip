@@ -82,11 +82,7 @@ __device__ __forceinline__ void lw_stage_links(const HopParams& P, const Nbr& nb
                 C u[9];
 #pragma unroll
                 for (int e = 0; e < (L12 ? 6 : 9); ++e) { u[e].x = (R)w[e].x; u[e].y = (R)w[e].y; }
-                if constexpr (L12) {
-                    u[6] = conj_(sub(mul(u[1], u[5]), mul(u[2], u[4])));
-                    u[7] = conj_(sub(mul(u[2], u[3]), mul(u[0], u[5])));
-                    u[8] = conj_(sub(mul(u[0], u[4]), mul(u[1], u[3])));
-                }
+                if constexpr (L12) complete_link(u);
                 // ph U for both hops: the backward one multiplies by (ph U)^dag
                 const int mu = t >> 1;
                 const C ph = edge[j] ? mk<C>((R)P.ph[mu][0], (R)P.ph[mu][1]) : mk<C>(R(1), R(0));
@@ -121,12 +117,13 @@ __device__ __forceinline__ void lw_step(const HopParams& P, const C (&lk)[8][9][
     constexpr int SF = DAG ? -1 : 1;
     load_spinor<SP>(K + 1 < 8 ? in : in_next, P.g.vh, no.o[(K + 1) & 7], ring[(K + 1) & 1]);
     __builtin_amdgcn_sched_barrier(0);
-    C p[12], u[9];
-    ring[K & 1].unpack(p);
-    if constexpr (SP == P_F16) pin_values(p, 12);
+    constexpr bool FWD = (K & 1) == 0;
+    constexpr int S = FWD ? SF : -SF;
+    C h[6], u[9];
+    project_raw<SP, MU, S>(ring[K & 1], h);
 #pragma unroll
     for (int e = 0; e < 9; ++e) u[e] = lk[K][e][lane];
-    hop_dir<MU, (K & 1) == 0 ? SF : -SF, (K & 1) == 0, false, C, false>(p, u, false, C{}, acc);
+    hop_half<MU, S, FWD, PH_REAL, false>(h, u, false, C{}, acc);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (K + 1 < 8) lw_step<SP, DAG, K + 1>(P, lk, lane, in, in_next, no, ring, acc);
 }

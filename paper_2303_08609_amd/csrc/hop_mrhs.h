@@ -81,12 +81,12 @@ __device__ __forceinline__ void link16_of(const RawRec<P_F16, L12 ? 6 : 9, true>
     if constexpr (Rec<P_F16, NW>::TAILB == 8) { w[4 * Rec<P_F16, NW>::NFULL] = r.t8.x; w[4 * Rec<P_F16, NW>::NFULL + 1] = r.t8.y; }
     if constexpr (Rec<P_F16, NW>::TAILB == 4) w[4 * Rec<P_F16, NW>::NFULL] = r.t4;
     if constexpr (L12) {
-        float2 u[6];
+        float2 u[9];
 #pragma unroll
         for (int k = 0; k < 6; ++k) u[k] = h2_to_f2(w[k]);
-        w[6] = f2_to_h2(conj_(sub(mul(u[1], u[5]), mul(u[2], u[4]))));
-        w[7] = f2_to_h2(conj_(sub(mul(u[2], u[3]), mul(u[0], u[5]))));
-        w[8] = f2_to_h2(conj_(sub(mul(u[0], u[4]), mul(u[1], u[3]))));
+        complete_link(u);
+#pragma unroll
+        for (int k = 6; k < 9; ++k) w[k] = f2_to_h2(u[k]);
     }
     if constexpr (CPH) {
         const float2 f = edge ? ph : make_float2(1.f, 0.f);

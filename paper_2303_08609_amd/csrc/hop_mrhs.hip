@@ -79,21 +79,16 @@ __device__ __forceinline__ void mrhs_consume(const MrhsParams& M, const Nbr& nb,
         if constexpr (hop_pin_f16<SP, LP, L12>() && LP == P_F16) pin_values(w, L12 ? 6 : 9);
 #pragma unroll
         for (int k = 0; k < (L12 ? 6 : 9); ++k) { u[k].x = (R)w[k].x; u[k].y = (R)w[k].y; }
-        if constexpr (L12) {
-            u[6] = conj_(sub(mul(u[1], u[5]), mul(u[2], u[4])));
-            u[7] = conj_(sub(mul(u[2], u[3]), mul(u[0], u[5])));
-            u[8] = conj_(sub(mul(u[0], u[4]), mul(u[1], u[3])));
-        }
+        if constexpr (L12) complete_link(u);
         const C ph = nb.edge[K] ? mk<C>((R)P.ph[MU][0], (R)P.ph[MU][1]) : mk<C>(R(1), R(0));
 #pragma unroll
         for (int k = 0; k < 9; ++k) u[k] = mul(ph, u[k]);
     }
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
-        C p[12];
-        r.sp[q].unpack(p);
-        if constexpr (hop_pin_f16<SP, LP, L12>() && SP == P_F16) pin_values(p, 12);
-        hop_dir<MU, FWD ? SF : -SF, FWD, false, C, false>(p, u, false, C{}, acc[q]);
+        C h[6];
+        project_raw<SP, MU, FWD ? SF : -SF>(r.sp[q], h);
+        hop_half<MU, FWD ? SF : -SF, FWD, PH_REAL, false>(h, u, false, C{}, acc[q]);
     }
 }
 
@@ -198,26 +193,23 @@ __device__ __forceinline__ void lr_consume(const HopParams& P, const Nbr& nb,
     constexpr int MU = K / 2;
     constexpr int SF = DAG ? -1 : 1;
     using R = decltype(C().x);
-    C p[12], u[9];
-    sp.unpack(p);
-    if constexpr (hop_pin_f16<SP, LP, L12>() && SP == P_F16) pin_values(p, 12);
+    constexpr bool FWD = (K & 1) == 0;
+    constexpr int S = FWD ? SF : -SF;
+    C h[6], u[9];
+    project_raw<SP, MU, S>(sp, h);
     {
         cx<typename St<LP>::real> w[9];
         ln.unpack(w);
         if constexpr (hop_pin_f16<SP, LP, L12>() && LP == P_F16) pin_values(w, L12 ? 6 : 9);
 #pragma unroll
         for (int k = 0; k < (L12 ? 6 : 9); ++k) { u[k].x = (R)w[k].x; u[k].y = (R)w[k].y; }
-        if constexpr (L12) {
-            u[6] = conj_(sub(mul(u[1], u[5]), mul(u[2], u[4])));
-            u[7] = conj_(sub(mul(u[2], u[3]), mul(u[0], u[5])));
-            u[8] = conj_(sub(mul(u[0], u[4]), mul(u[1], u[3])));
-        }
+        if constexpr (L12) complete_link(u);
     }
     C phase;
     phase.x = (R)P.ph[MU][0];
     phase.y = (R)P.ph[MU][1];
-    if constexpr ((K & 1) == 0) hop_dir<MU, SF, true, CPH>(p, u, nb.edge[K], phase, acc);
-    else hop_dir<MU, -SF, false, CPH>(p, u, nb.edge[K], conj_(phase), acc);
+    if constexpr (!FWD) phase = conj_(phase);
+    hop_half<MU, S, FWD, CPH ? PH_CPLX : PH_REAL, true>(h, u, nb.edge[K], phase, acc);
 }
 
 // Neighbour records flow through a ring of D+1 slots (D+1 divides 8, so a

@@ -69,7 +69,7 @@ __device__ __forceinline__ void sap_term(const SapParams& P, const uint8_t* ubas
     const R pr = (R)P.ph[MU][0], pi = (R)(FWD ? P.ph[MU][1] : -P.ph[MU][1]);
     C w = nb.edge[K] ? mk<C>(pr, pi) : mk<C>(R(1), R(0));
     w = on ? w : mk<C>(R(0), R(0));
-    hop_dir<MU, FWD ? 1 : -1, FWD, true>(psi, u, true, w, acc);
+    hop_dir<MU, FWD ? 1 : -1, FWD, PH_CPLX>(psi, u, true, w, acc);
 }
 
 template <int SP, int LP, bool L12>
