@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(256, Waves<SP>::n > 0 ? Waves<SP>::n : 1) k_ho
 }
 
 // ------------------------------------------------------------------ host ----
-static TuneCfg g_hop_tune = {256, 1, 0};
+static TuneCfg g_hop_tune = {256, 1, -1};
 TuneCfg& hop_tune() { return g_hop_tune; }
 
 // Launch-shape overrides from the environment (WEO_HOP_BLOCK, WEO_HOP_REMAP,
@@ -71,6 +71,31 @@ static void read_env_tuning() {
         const int v = atoi(z);
         if (v >= 0 && v <= 64) g_hop_tune.bz = v;
     }
+}
+
+// z strips for lattices whose t slices outgrow an XCD's 4 MiB of L2: walked in
+// lexicographic order, a slice's spinors are gone before the next slice wants
+// them.  With 8 strips each of the 8 XCDs walks one strip through all of t
+// (with 4, half of t), so the strip's three slices stay in its L2 and only the
+// strip's edge planes are read twice.  Height Lz / 8 if that is 5 planes or
+// more (lower ones lose more at the edges than they gain), otherwise Lz / 4 of
+// 6 or more, otherwise none; other numbers of strips leave XCDs in the middle
+// of two strips.  Strips measured (apply, us, none -> strips; parity slice):
+//   FP16/12 48^3x96 (2.6 MB) 702 -> 672, FP32/12 48^3x64 (5.3) 927 -> 896,
+//   FP32/12 40^3x48 (3.1) 413 -> 400, FP32/12 64^3x24 (12.6) 863 -> 787,
+//   FP64/18 48^3x32 (10.6) 1302 -> 1179, FP64/12 32^3x64 (3.1) 618 -> 574;
+// in smaller slices they gain nothing or cost: FP32/18 32^3x64 (1.6) 290 -> 300,
+// FP64/18 24^3x96 (1.3) 468 -> 469, FP16/12 40^3x80 (1.5) 315 -> 314; hence the
+// line at 2.5 MB.  An XCD's walk of few slices gains little: 8 slices (FP32/18
+// 128x64x40x8) 406 -> 408, 14 (FP64/18 28x44x52x28) 632 -> 637, but 12
+// (FP64/18 64x64x32x24) 1158 -> 1059; hence 12.  The clover hop, with its block
+// reads, measured the same with and without (it keeps lexicographic order).
+int hop_strip(const Geom& g, int fmt) {
+    if (g_hop_tune.bz >= 0) return g_hop_tune.bz;
+    if (spinor_field_bytes(g, fmt) / (size_t)g.lt < 2500000) return 0;
+    if (g.lz % 8 == 0 && g.lz >= 40) return g.lt >= 12 ? g.lz / 8 : 0;
+    if (g.lz % 4 == 0 && g.lz >= 24) return g.lt >= 24 ? g.lz / 4 : 0;
+    return 0;
 }
 
 uint32_t hop_partials(const Geom& g) { return (g.vh + 63) / 64; }
@@ -132,7 +157,7 @@ hipError_t launch_hop_single(const HopLaunch& h, hipStream_t s) {
     P.partial = h.partial;
     P.spinor_bytes = spinor_field_bytes(h.g, h.fmt);
     P.link_block = gauge_block_bytes(h.g, h.fmt);
-    P.sched = make_sched(h.g, g_hop_tune.bz, (uint32_t)g_hop_tune.block, h.partial != nullptr);
+    P.sched = make_sched(h.g, hop_strip(h.g, h.fmt), (uint32_t)g_hop_tune.block, h.partial != nullptr);
     if (hop_is_small(h)) return launch_hop_small(h, P, s);
     const dim3 block(g_hop_tune.block);
     const dim3 grid(P.sched.nblk, h.nrhs);

@@ -153,7 +153,7 @@ hipError_t launch_hop_clover_single(const HopLaunch& h, hipStream_t s) {
     P.partial = h.partial;
     P.spinor_bytes = spinor_field_bytes(h.g, h.fmt);
     P.link_block = gauge_block_bytes(h.g, h.fmt);
-    P.sched = make_sched(h.g, tc.bz, (uint32_t)tc.block, h.partial != nullptr);
+    P.sched = make_sched(h.g, tc.bz > 0 ? tc.bz : 0, (uint32_t)tc.block, h.partial != nullptr);
     if (hop_is_small(h)) return launch_hop_small(h, P, s);
     Q.block_bytes = clover_block_bytes(h.g, h.fmt);
     Q.clv = static_cast<const uint8_t*>(h.clv) + (size_t)(2 * h.out_par) * Q.block_bytes;

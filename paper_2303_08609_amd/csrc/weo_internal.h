@@ -62,9 +62,10 @@ struct HopLaunch {
 struct TuneCfg {
     int block;    // threads per workgroup (multiple of 64, <= 256)
     int remap;    // XCD-aware workgroup remap on/off
-    int bz;       // workgroup schedule: z-strip height (0 = lexicographic)
+    int bz;       // workgroup schedule: z-strip height (0 = lexicographic, -1 = hop_strip's)
 };
 TuneCfg& hop_tune();                       // current single-rhs launch shape
+int hop_strip(const Geom& g, int fmt);     // the Wilson hop's z-strip height (0 = none)
 uint32_t hop_partials(const Geom& g);      // norm partials per rhs: one per 64 sites
 hipError_t launch_hop(const HopLaunch& h, hipStream_t s);          // picks the kernel
 hipError_t launch_hop_single(const HopLaunch& h, hipStream_t s);   // one lane per site
