@@ -206,6 +206,14 @@ __global__ void k_zero(uint4* p, size_t n16) {
     if (i < n16) p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+__global__ void k_set_status(SolveStatus* d, int nrhs, uint32_t live, int fresh, double bb) {
+    const int r = threadIdx.x;
+    if (r >= nrhs) return;
+    d->mask[r] = (int)(live >> r & 1u);
+    if (fresh) d->flags[r] = 0;
+    if (bb >= 0.0) d->bb[r] = bb;
+}
+
 // out[r] = sum_b partial[r][b] in a fixed order (one workgroup per rhs).
 // The final sums run in one workgroup per rhs; 1024 lanes keep the strided
 // first pass short when there are tens of thousands of partials.
@@ -716,6 +724,12 @@ hipError_t launch_convert(const Geom& g, int fmt_in, const void* in, int fmt_out
         case P_BF16: return convert_to<P_BF16>(g, po, fbi, fbo, I, O, nrhs, scale, accumulate, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_set_status(SolveStatus* d, int nrhs, uint32_t live, bool fresh, double bb, hipStream_t st) {
+    static_assert(kMaxRhs <= 32, "one bit per right-hand side");
+    hipLaunchKernelGGL(k_set_status, dim3(1), dim3(64), 0, st, d, nrhs, live, (int)fresh, bb);
+    return hipGetLastError();
 }
 
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st) {

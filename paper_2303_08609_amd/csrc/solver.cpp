@@ -91,6 +91,7 @@ struct Scalars {
     double *gamma, *alpha, *beta, *ss, *bb, *rr, *sc_in, *sc_out, *nrm;
     double *crho, *calpha, *comega, *cbeta;     // BiCGStab complex scalars (re, im)
     int *mask, *flags;
+    SolveStatus* status;                        // bb, ss, nrm, mask and flags lie in it
 };
 
 struct Workspace {
@@ -174,13 +175,16 @@ Workspace carve_ws(const Geom& g, int fmt, const weo_solver_params* p, int inner
     w.pa = static_cast<double*>(c.take(np));
     w.pb = static_cast<double*>(c.take(np));
     w.pc = static_cast<double*>(c.take(np));
-    double* d = static_cast<double*>(c.take(17 * WEO_MAX_RHS * sizeof(double)));
-    int* ip = static_cast<int*>(c.take(2 * WEO_MAX_RHS * sizeof(int)));
+    double* d = static_cast<double*>(c.take(14 * WEO_MAX_RHS * sizeof(double)));
+    SolveStatus* st = static_cast<SolveStatus*>(c.take(sizeof(SolveStatus)));
     if (d) {
-        w.sc.gamma = d; w.sc.alpha = d + 16; w.sc.beta = d + 32; w.sc.ss = d + 48; w.sc.bb = d + 64;
-        w.sc.rr = d + 80; w.sc.sc_in = d + 96; w.sc.sc_out = d + 112; w.sc.nrm = d + 128;
-        w.sc.crho = d + 144; w.sc.calpha = d + 176; w.sc.comega = d + 208; w.sc.cbeta = d + 240;
-        w.sc.mask = ip; w.sc.flags = ip + 16;
+        constexpr int N = WEO_MAX_RHS;
+        static_assert(N == kMaxRhs, "status block");
+        w.sc.gamma = d; w.sc.alpha = d + N; w.sc.beta = d + 2 * N; w.sc.rr = d + 3 * N;
+        w.sc.sc_in = d + 4 * N; w.sc.sc_out = d + 5 * N;
+        w.sc.crho = d + 6 * N; w.sc.calpha = d + 8 * N; w.sc.comega = d + 10 * N; w.sc.cbeta = d + 12 * N;
+        w.sc.status = st;
+        w.sc.bb = st->bb; w.sc.ss = st->ss; w.sc.nrm = st->nrm; w.sc.mask = st->mask; w.sc.flags = st->flags;
     }
     w.bytes = c.off;
     return w;
@@ -337,28 +341,41 @@ struct LevelResult {
     int breakdown;
 };
 
-// Host look at the residual norms: masks off converged rhs, notes breakdowns.
-// Returns the number of live rhs (or a negative status); ss and mask are
-// left holding what was seen.
-int look_at(Ctx& c, const Workspace& w, int nrhs, double tol2, const std::vector<double>& bb,
-            std::vector<double>& ss, std::vector<int>& mask, LevelResult* res) {
-    std::vector<int> flags(nrhs);
-    HIPCHK(hipMemcpyAsync(ss.data(), w.sc.ss, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipMemcpyAsync(mask.data(), w.sc.mask, nrhs * sizeof(int), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipMemcpyAsync(flags.data(), w.sc.flags, nrhs * sizeof(int), hipMemcpyDeviceToHost, c.st));
+// The solve's status on the host, in one copy; waits for the stream.
+int read_status(Ctx& c, const Workspace& w, SolveStatus* h) {
+    HIPCHK(hipMemcpyAsync(h, w.sc.status, sizeof(*h), hipMemcpyDeviceToHost, c.st));
     HIPCHK(hipStreamSynchronize(c.st));
+    return WEO_OK;
+}
+
+uint32_t live_bits(const SolveStatus& h, int nrhs) {
+    uint32_t bits = 0;
+    for (int r = 0; r < nrhs; ++r) bits |= (uint32_t)(h.mask[r] != 0) << r;
+    return bits;
+}
+
+// Masks off the rhs of h whose residual meets the tolerance, there and on the
+// device; returns the number of live ones (or a negative status).
+int mask_converged(Ctx& c, const Workspace& w, int nrhs, double tol2, SolveStatus* h) {
     int live = 0;
     bool changed = false;
     for (int r = 0; r < nrhs; ++r) {
-        if (flags[r]) res->breakdown = 1;
-        if (mask[r] && ss[r] <= tol2 * bb[r]) { mask[r] = 0; changed = true; }
-        live += mask[r] != 0;
+        if (h->mask[r] && h->ss[r] <= tol2 * h->bb[r]) { h->mask[r] = 0; changed = true; }
+        live += h->mask[r] != 0;
     }
-    if (changed) {
-        HIPCHK(hipMemcpyAsync(w.sc.mask, mask.data(), nrhs * sizeof(int), hipMemcpyHostToDevice, c.st));
-        HIPCHK(hipStreamSynchronize(c.st));     // the host vector goes out of scope
-    }
+    if (changed) HIPCHK(launch_set_status(w.sc.status, nrhs, live_bits(*h, nrhs), false, -1.0, c.st));
     return live;
+}
+
+// Host look at the residual norms: masks off converged rhs, notes breakdowns.
+// Returns the number of live rhs (or a negative status); h is left holding
+// what was seen.
+int look_at(Ctx& c, const Workspace& w, int nrhs, double tol2, SolveStatus* h, LevelResult* res) {
+    const int rc = read_status(c, w, h);
+    if (rc != WEO_OK) return rc;
+    for (int r = 0; r < nrhs; ++r)
+        if (h->flags[r]) res->breakdown = 1;
+    return mask_converged(c, w, nrhs, tol2, h);
 }
 
 // When the host next looks at the residuals.  The look costs a stream
@@ -371,20 +388,19 @@ int look_at(Ctx& c, const Workspace& w, int nrhs, double tol2, const std::vector
 struct LookPlan {
     int every, last_it = 0;
     std::vector<double> last_ss;
-    LookPlan(int check_every, const std::vector<double>& ss0) : every(check_every), last_ss(ss0) {}
+    LookPlan(int check_every, const SolveStatus& h, int nrhs) : every(check_every), last_ss(h.ss, h.ss + nrhs) {}
     int first() const { return every < 2 ? every : 2; }
-    int next(int it, const std::vector<double>& ss, const std::vector<int>& mask, const std::vector<double>& bb,
-             double tol2) {
+    int next(int it, const SolveStatus& h, double tol2) {
         double need = 1.0;
-        for (size_t r = 0; r < ss.size(); ++r) {
-            if (!mask[r]) continue;
-            const double a = last_ss[r], b = ss[r], goal = tol2 * bb[r];
+        for (size_t r = 0; r < last_ss.size(); ++r) {
+            if (!h.mask[r]) continue;
+            const double a = last_ss[r], b = h.ss[r], goal = tol2 * h.bb[r];
             if (!(a > 0.0) || !(b > 0.0) || !(b < a) || it <= last_it) { need = every; break; }
             const double rate = std::log(b / a) / (double)(it - last_it);   // per iteration, < 0
             const double k = std::log(goal / b) / rate;
             if (k > need) need = k;
         }
-        last_ss = ss;
+        last_ss.assign(h.ss, h.ss + last_ss.size());
         last_it = it;
         const int k = need >= (double)every ? every : (int)std::ceil(need);
         return it + (k < 1 ? 1 : k);
@@ -417,27 +433,17 @@ int run_level(Ctx& c, const Workspace& w, int op, int fmt_op, int fmt_acc, const
     HIPCHK(launch_reduce(w.pa, op != WEO_OP_MDAGM ? (int)nbh : (int)nbb, nrhs, w.sc.gamma, c.st));
     HIPCHK(launch_convert(g, fmt_op, w.r, fmt_op, w.p, nrhs, nullptr, 0, c.st));
 
-    std::vector<double> ss(nrhs), bb(nrhs);
-    std::vector<int> mask(nrhs);
+    SolveStatus h;
     const double tol2 = tol * tol;
     // a start that already meets the tolerance costs no iteration
     HIPCHK(launch_norm2(g, fmt_acc, w.s_acc, nrhs, w.pb, c.st));
     HIPCHK(launch_reduce(w.pb, (int)nbb, nrhs, w.sc.ss, c.st));
-    HIPCHK(hipMemcpyAsync(ss.data(), w.sc.ss, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipMemcpyAsync(bb.data(), w.sc.bb, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipMemcpyAsync(mask.data(), w.sc.mask, nrhs * sizeof(int), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
-    {
-        int live = 0;
-        for (int r = 0; r < nrhs; ++r) {
-            if (mask[r] && ss[r] <= tol2 * bb[r]) mask[r] = 0;
-            live += mask[r] != 0;
-        }
-        HIPCHK(hipMemcpyAsync(w.sc.mask, mask.data(), nrhs * sizeof(int), hipMemcpyHostToDevice, c.st));
-        HIPCHK(hipStreamSynchronize(c.st));
-        if (!live) return WEO_OK;
-    }
-    LookPlan plan(check_every, ss);
+    const int rc = read_status(c, w, &h);
+    if (rc != WEO_OK) return rc;
+    int live = mask_converged(c, w, nrhs, tol2, &h);
+    if (live < 0) return live;
+    if (!live) return WEO_OK;
+    LookPlan plan(check_every, h, nrhs);
     int look = plan.first();
     for (int it = 1; it <= maxiter; ++it) {
         // q = A p with the alpha denominator in pa
@@ -463,13 +469,12 @@ int run_level(Ctx& c, const Workspace& w, int op, int fmt_op, int fmt_acc, const
         }
         res->iters = it;
         if (it == look || it == maxiter) {
-            const int live = look_at(c, w, nrhs, tol2, bb, ss, mask, res);
+            live = look_at(c, w, nrhs, tol2, &h, res);
             if (live < 0) return live;
             if (!live) break;
-            look = plan.next(it, ss, mask, bb, tol2);
+            look = plan.next(it, h, tol2);
         }
     }
-    HIPCHK(hipStreamSynchronize(c.st));
     return WEO_OK;
 }
 
@@ -491,17 +496,14 @@ int run_level_bicg(Ctx& c, const Workspace& w, int op, int fmt_op, int fmt_acc, 
     B.ss = w.sc.ss; B.bb = w.sc.bb; B.tol2 = tol2; B.mask = w.sc.mask; B.flags = w.sc.flags;
     res->iters = 0;
     res->breakdown = 0;
-    std::vector<double> ss(nrhs);
-    std::vector<int> mask(nrhs);
-    std::vector<double> bb(nrhs);
-    HIPCHK(hipMemcpyAsync(bb.data(), w.sc.bb, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
+    SolveStatus h;
     // r^ = r (rounded to fmt_op), p = r, rho = <r^, r>, in one pass
     HIPCHK(launch_bi_init(g, fmt_acc, fmt_op, nrhs, w.sc.mask, w.s_acc, w.rh, w.p, w.pa, w.pb, w.pc, c.st));
     HIPCHK(launch_bi_scalars(BI_INIT, B, nbb, w.pa, w.pb, w.pc, c.st));
-    int live = look_at(c, w, nrhs, tol2, bb, ss, mask, res);
+    int live = look_at(c, w, nrhs, tol2, &h, res);
     if (live < 0) return live;
     if (!live) return WEO_OK;
-    LookPlan plan(check_every, ss);
+    LookPlan plan(check_every, h, nrhs);
     int look = plan.first();
     // Wilson M with every vector in one format: <r^, v> and (<t, s>, ||t||^2)
     // come from the epilogues of the operator's second hop (the dot partner
@@ -536,13 +538,12 @@ int run_level_bicg(Ctx& c, const Workspace& w, int op, int fmt_op, int fmt_acc, 
         HIPCHK(launch_bi_p(g, fmt_acc, fmt_op, nrhs, B, w.s_acc, w.p, w.q, c.st));
         res->iters = it;
         if (it == look || it == maxiter) {
-            live = look_at(c, w, nrhs, tol2, bb, ss, mask, res);
+            live = look_at(c, w, nrhs, tol2, &h, res);
             if (live < 0) return live;
             if (!live) break;
-            look = plan.next(it, ss, mask, bb, tol2);
+            look = plan.next(it, h, tol2);
         }
     }
-    HIPCHK(hipStreamSynchronize(c.st));
     return WEO_OK;
 }
 
@@ -700,20 +701,15 @@ int run_level_block(Ctx& c, const Workspace& w, int op, int fmt, const void* u, 
     const size_t fb = spinor_field_bytes(g, fmt);
     res->iters = 0;
     res->breakdown = 0;
-    std::vector<int> mask(nrhs);
-    std::vector<double> bb(nrhs);
-    HIPCHK(hipMemcpyAsync(mask.data(), w.sc.mask, nrhs * sizeof(int), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipMemcpyAsync(bb.data(), w.sc.bb, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
     // rhs whose start already meets the tolerance stay out of the block
-    std::vector<double> ss0(nrhs);
+    SolveStatus h;
     HIPCHK(launch_norm2(g, fmt, w.s_acc, nrhs, w.pb, c.st));
-    HIPCHK(launch_reduce(w.pb, (int)blas_blocks(g), nrhs, w.sc.rr, c.st));
-    HIPCHK(hipMemcpyAsync(ss0.data(), w.sc.rr, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
+    HIPCHK(launch_reduce(w.pb, (int)blas_blocks(g), nrhs, w.sc.ss, c.st));
+    const int rc = read_status(c, w, &h);
+    if (rc != WEO_OK) return rc;
     std::vector<int> live;
     for (int r = 0; r < nrhs; ++r)
-        if (mask[r] && !(ss0[r] <= tol * tol * bb[r])) live.push_back(r);
+        if (h.mask[r] && !(h.ss[r] <= tol * tol * h.bb[r])) live.push_back(r);
     const int s = (int)live.size();
     if (!s) return WEO_OK;
     const bool normal = op != WEO_OP_MDAGM;
@@ -796,7 +792,7 @@ int run_level_block(Ctx& c, const Workspace& w, int op, int fmt, const void* u, 
             if (normal) rr = ssv[j];
             else
                 for (int i = 0; i < s; ++i) rr += std::norm(cm(i, j));
-            if (!(rr <= tol2 * bb[live[j]])) return false;
+            if (!(rr <= tol2 * h.bb[live[j]])) return false;
         }
         return true;
     };
@@ -877,11 +873,11 @@ int run_level_gcr(Ctx& c, const Workspace& w, int fmt, const void* u, void* x_ac
     const bool conv = c.fmt_pre != fmt;
     res->iters = 0;
     res->breakdown = 0;
-    std::vector<int> mask(nrhs);
-    std::vector<double> bb(nrhs);
-    HIPCHK(hipMemcpyAsync(mask.data(), w.sc.mask, nrhs * sizeof(int), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipMemcpyAsync(bb.data(), w.sc.bb, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));
+    SolveStatus h;
+    const int rc = read_status(c, w, &h);
+    if (rc != WEO_OK) return rc;
+    const int* mask = h.mask;
+    const double* bb = h.bb;
     std::vector<double> sums(2 * kGcrMax);
     auto fetch = [&](int nval) -> hipError_t {
         hipError_t e = launch_reduce(w.gcpart, (int)nwg, nval, w.gcsum, c.st);
@@ -992,14 +988,6 @@ int true_resid(Ctx& c, const Workspace& w, int op, int fmt, const void* u, const
     HIPCHK(hipMemcpyAsync(bb.data(), w.sc.bb, nrhs * sizeof(double), hipMemcpyDeviceToHost, c.st));
     HIPCHK(hipStreamSynchronize(c.st));
     for (int r = 0; r < nrhs; ++r) out[r] = bb[r] > 0 ? std::sqrt(rr[r] / bb[r]) : std::sqrt(rr[r]);
-    return WEO_OK;
-}
-
-int set_mask(Ctx& c, const Workspace& w, const std::vector<int>& mask) {
-    std::vector<int> zero(mask.size(), 0);
-    HIPCHK(hipMemcpyAsync(w.sc.mask, mask.data(), mask.size() * sizeof(int), hipMemcpyHostToDevice, c.st));
-    HIPCHK(hipMemcpyAsync(w.sc.flags, zero.data(), zero.size() * sizeof(int), hipMemcpyHostToDevice, c.st));
-    HIPCHK(hipStreamSynchronize(c.st));   // host vectors go out of scope
     return WEO_OK;
 }
 
@@ -1130,7 +1118,6 @@ extern "C" int wilson_eo_cg(const weo_lattice* lat, const weo_format* fmt, const
     c.fmt_pre = pre64 ? inner : (p->mixed ? inner : id);
     c.u_pre = (pre64 || p->mixed) ? u_inner : u;
     const uint32_t nbb = blas_blocks(gb);
-    std::vector<int> live(n, 1);
     int status = WEO_OK;
 
     // bb = ||b||^2
@@ -1146,7 +1133,7 @@ extern "C" int wilson_eo_cg(const weo_lattice* lat, const weo_format* fmt, const
             HIPCHK(launch_zero(x, fb, c.st));
             HIPCHK(launch_convert(gb, id, b, id, w.s_acc, n, nullptr, 0, c.st));
         }
-        if ((rc = set_mask(c, w, live)) != WEO_OK) return rc;
+        HIPCHK(launch_set_status(w.sc.status, n, ~0u, true, -1.0, c.st));
         LevelResult lr;
         if ((rc = run_method(c, w, p->method, p->op, id, id, u, x, n, p->tol, p->maxiter, p->check_every,
                              &lr)) != WEO_OK)
@@ -1171,8 +1158,6 @@ extern "C" int wilson_eo_cg(const weo_lattice* lat, const weo_format* fmt, const
         int inner_iters = 0, k = 0;
         bool breakdown = false;
         std::vector<double> rel(n), bb0(n);
-        HIPCHK(hipMemcpyAsync(bb0.data(), w.sc.bb, n * sizeof(double), hipMemcpyDeviceToHost, c.st));
-        HIPCHK(hipStreamSynchronize(c.st));
         const size_t f1 = spinor_field_bytes(gb, id), fa1 = spinor_field_bytes(gb, kAccF32);
         const bool can_compact = p->op != WEO_OP_MDAGM;
         // the Wilson M residual in one fused pass (site blocks and D_W take
@@ -1209,9 +1194,10 @@ extern "C" int wilson_eo_cg(const weo_lattice* lat, const weo_format* fmt, const
             ScalarArgsHost sa = sargs(w.sc, m);
             sa.pa = w.pa; sa.nba = nba; sa.target = target;
             HIPCHK(launch_scalars(SCAL_SCALE, sa, c.st));
-            std::vector<double> rr(m);
-            HIPCHK(hipMemcpyAsync(rr.data(), w.sc.nrm, m * sizeof(double), hipMemcpyDeviceToHost, c.st));
-            HIPCHK(hipStreamSynchronize(c.st));
+            SolveStatus h;
+            if ((rc = read_status(c, w, &h)) != WEO_OK) return rc;
+            const double* rr = h.nrm;
+            if (k == 0) bb0.assign(h.bb, h.bb + n);     // later: the inner solve's
             std::vector<int> keep;          // compact slots still live
             double worst = 0.0;
             for (int j = 0; j < m; ++j) {
@@ -1246,12 +1232,11 @@ extern "C" int wilson_eo_cg(const weo_lattice* lat, const weo_format* fmt, const
             }
             HIPCHK(launch_zero(w.x_acc, (size_t)mi * fa1, c.st));
             // the inner stopping test compares with ||rhs||^2 = target
-            std::vector<double> tg(mi, target);
-            HIPCHK(hipMemcpyAsync(w.sc.bb, tg.data(), mi * sizeof(double), hipMemcpyHostToDevice, c.st));
-            std::vector<int> mask(mi, 1);
+            uint32_t bits = ~0u;
             if (!can_compact)
-                for (int j = 0; j < mi; ++j) mask[j] = !(rel[cur[j]] <= p->tol);
-            if ((rc = set_mask(c, w, mask)) != WEO_OK) return rc;
+                for (int j = 0; j < mi; ++j)
+                    if (rel[cur[j]] <= p->tol) bits &= ~(1u << j);
+            HIPCHK(launch_set_status(w.sc.status, mi, bits, true, target, c.st));
             // The inner tolerance: inner_tol, tightened (down to inner_tol / 8)
             // for a step whose solve can then bring every live rhs to tol --
             // one inner solve a little longer instead of one more outer step

@@ -111,6 +111,21 @@ hipError_t launch_convert(const Geom& g, int fmt_in, const void* in, int fmt_out
 // clear bytes (a multiple of 16) with a kernel (safe inside graph capture)
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 
+// What the host sees of a running solve, one copy of 512 bytes: three small
+// copies at each look cost 17 us and 3.6 us each on the device.
+constexpr int kMaxRhs = 16;
+struct SolveStatus {
+    double bb[kMaxRhs];     // ||b||^2 of the stopping test
+    double ss[kMaxRhs];     // ||s||^2 (or ||r||^2)
+    double nrm[kMaxRhs];    // ||r64||^2 (SCAL_SCALE)
+    int mask[kMaxRhs];      // live right-hand sides
+    int flags[kMaxRhs];     // 1: breakdown
+};
+// mask = the low nrhs bits of live; fresh: also flags = 0; bb >= 0: also every
+// bb = bb.  A kernel: values passed with the launch need no host memory that
+// outlives it, so nothing waits for the stream.
+hipError_t launch_set_status(SolveStatus* d, int nrhs, uint32_t live, bool fresh, double bb, hipStream_t s);
+
 // Solver scalar steps, one workgroup per rhs:
 //   SCAL_ALPHA: a = sum pa;  alpha = gamma / a (breakdown if a <= 0 or not finite)
 //   SCAL_BETA:  a = sum pa, b = sum pb;  beta = a / gamma; gamma = a;
