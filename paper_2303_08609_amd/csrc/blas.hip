@@ -316,26 +316,26 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
 __device__ __forceinline__ double2 cget(const double* p, int r) { return make_double2(p[2 * r], p[2 * r + 1]); }
 __device__ __forceinline__ void cset(double* p, int r, double2 v) { p[2 * r] = v.x; p[2 * r + 1] = v.y; }
 
-// Sums three values over the workgroup in a fixed order; results in thread 0.
-__device__ __forceinline__ void group_sum3(double a, double b, double c, double* out) {
-    __shared__ double lds[3][16];
-    a = wave_sum(a);
-    b = wave_sum(b);
-    c = wave_sum(c);
-    if ((threadIdx.x & 63) == 0) {
-        lds[0][threadIdx.x >> 6] = a;
-        lds[1][threadIdx.x >> 6] = b;
-        lds[2][threadIdx.x >> 6] = c;
+// Sums N values over the workgroup in a fixed order; results in thread 0.
+template <int N> __device__ __forceinline__ void group_sums(const double* v, double* out) {
+    __shared__ double lds[16][N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const double t = wave_sum(v[q]);
+        if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6][q] = t;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        out[0] = out[1] = out[2] = 0.0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            out[0] += lds[0][w];
-            out[1] += lds[1][w];
-            out[2] += lds[2][w];
-        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) out[q] = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w)
+#pragma unroll
+            for (int q = 0; q < N; ++q) out[q] += lds[w][q];
     }
+}
+__device__ __forceinline__ void group_sum3(double a, double b, double c, double* out) {
+    const double v[3] = {a, b, c};
+    group_sums<3>(v, out);
 }
 
 struct BiArgs {
@@ -417,70 +417,74 @@ __global__ void __launch_bounds__(kBlk) k_bi_init(Fields F, const int* __restric
     }
 }
 
-// s = r - alpha v  [s_op = s];  partial = ||s||^2
+// s = r - alpha v  [s_op = s]
 template <int ACC, int OP, bool SOP>
 __global__ void __launch_bounds__(kBlk) k_bi_s(Fields F, BiArgs B, const uint8_t* rv, const uint8_t* v,
-                                               uint8_t* s, uint8_t* s_op, double* partial) {
+                                               uint8_t* s, uint8_t* s_op) {
     using RA = typename AR<ACC>::R;
     using CA = cx<RA>;
     using CO = cx<typename AR<OP>::R>;
     const int r = blockIdx.y;
     const uint32_t i = blockIdx.x * kBlk + threadIdx.x;
-    double nrm = 0.0;
-    if (bi_live(B.mask, r) && i < F.vh) {
-        const double2 al = cget(B.alpha, r);
-        const RA ar = (RA)al.x, ai = (RA)al.y;
-        CA rr[12];
-        CO vv[12];
-        load_rec<ACC, 12>(rv + (size_t)r * F.fb_acc, F.vh, i, rr);
-        load_rec<OP, 12>(v + (size_t)r * F.fb_op, F.vh, i, vv);
+    if (!bi_live(B.mask, r) || i >= F.vh) return;
+    const double2 al = cget(B.alpha, r);
+    const RA ar = (RA)al.x, ai = (RA)al.y;
+    CA rr[12];
+    CO vv[12];
+    load_rec<ACC, 12>(rv + (size_t)r * F.fb_acc, F.vh, i, rr);
+    load_rec<OP, 12>(v + (size_t)r * F.fb_op, F.vh, i, vv);
 #pragma unroll
-        for (int k = 0; k < 12; ++k) {
-            const RA vx = (RA)vv[k].x, vy = (RA)vv[k].y;
-            rr[k].x = rr[k].x - (ar * vx - ai * vy);
-            rr[k].y = rr[k].y - (ar * vy + ai * vx);
-        }
-        store_rec<ACC, 12>(s + (size_t)r * F.fb_acc, F.vh, i, rr);
-        if constexpr (SOP) {
-            CO so[12];
-            cvt12(rr, so);
-            store_rec<OP, 12>(s_op + (size_t)r * F.fb_op, F.vh, i, so);
-        }
-        nrm = norm2_12(rr);
+    for (int k = 0; k < 12; ++k) {
+        const RA vx = (RA)vv[k].x, vy = (RA)vv[k].y;
+        rr[k].x = rr[k].x - (ar * vx - ai * vy);
+        rr[k].y = rr[k].y - (ar * vy + ai * vx);
     }
-    const double t = group_sum(nrm);
-    if (threadIdx.x == 0) partial[(size_t)r * gridDim.x + blockIdx.x] = t;
+    store_rec<ACC, 12>(s + (size_t)r * F.fb_acc, F.vh, i, rr);
+    if constexpr (SOP) {
+        CO so[12];
+        cvt12(rr, so);
+        store_rec<OP, 12>(s_op + (size_t)r * F.fb_op, F.vh, i, so);
+    }
 }
 
-// partials <t, s> (re, im) and ||t||^2; t in OP, s in ACC
-template <int ACC, int OP>
+// Partials <t, s> (re, im) and ||t||^2; t in OP, s in ACC.  RH: also <r^, s>
+// and <r^, t> (r^ in OP), from which the next rho = <r^, s - omega t> follows
+// without waiting for r.  Value v of rhs r at part[(v nrhs + r) blocks + block].
+template <int ACC, int OP, bool RH>
 __global__ void __launch_bounds__(kBlk) k_bi_ts(Fields F, const int* __restrict__ mask, const uint8_t* t,
-                                                const uint8_t* s, double* pre, double* pim, double* ptt) {
+                                                const uint8_t* s, const uint8_t* rh, double* part) {
     using CA = cx<typename AR<ACC>::R>;
     using CO = cx<typename AR<OP>::R>;
+    constexpr int NV = RH ? 7 : 3;
     const int r = blockIdx.y;
     const uint32_t i = blockIdx.x * kBlk + threadIdx.x;
-    double re = 0.0, im = 0.0, tt = 0.0;
+    double v[NV] = {};
     if (bi_live(mask, r) && i < F.vh) {
-        CO tv[12];
+        CO tv[12], hv[RH ? 12 : 1];
         CA sv[12];
         load_rec<OP, 12>(t + (size_t)r * F.fb_op, F.vh, i, tv);
         load_rec<ACC, 12>(s + (size_t)r * F.fb_acc, F.vh, i, sv);
+        if constexpr (RH) load_rec<OP, 12>(rh + (size_t)r * F.fb_op, F.vh, i, hv);
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
             const double tx = tv[k].x, ty = tv[k].y, sx = sv[k].x, sy = sv[k].y;
-            re += tx * sx + ty * sy;
-            im += tx * sy - ty * sx;
-            tt += tx * tx + ty * ty;
+            v[0] += tx * sx + ty * sy;
+            v[1] += tx * sy - ty * sx;
+            v[2] += tx * tx + ty * ty;
+            if constexpr (RH) {
+                const double hx = hv[k].x, hy = hv[k].y;
+                v[3] += hx * sx + hy * sy;
+                v[4] += hx * sy - hy * sx;
+                v[5] += hx * tx + hy * ty;
+                v[6] += hx * ty - hy * tx;
+            }
         }
     }
-    double out[3];
-    group_sum3(re, im, tt, out);
+    double out[NV];
+    group_sums<NV>(v, out);
     if (threadIdx.x == 0) {
-        const size_t o = (size_t)r * gridDim.x + blockIdx.x;
-        pre[o] = out[0];
-        pim[o] = out[1];
-        ptt[o] = out[2];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) part[((size_t)q * gridDim.y + r) * gridDim.x + blockIdx.x] = out[q];
     }
 }
 
@@ -567,52 +571,147 @@ __global__ void __launch_bounds__(kBlk) k_bi_p(Fields F, BiArgs B, const uint8_t
     store_rec<OP, 12>(prow, F.vh, i, po);
 }
 
-// Scalar steps, one workgroup per rhs; pa, pb, pc are [nrhs][nb] partials.
-//   BI_INIT:  pa = ||r||^2, pb, pc = <r^, r> -> ss, rho = <r^, r>, alpha = omega = 1
-//   BI_ALPHA: pa, pb = <r^, v>     -> alpha = rho / <r^, v>
-//   BI_OMEGA: pa, pb = <t, s>, pc = ||t||^2 -> omega = <t, s> / ||t||^2 (0 if t = 0)
-//   BI_BETA:  pa = ||r||^2, pb, pc = <r^, r> -> ss, beta = (rho'/rho)(alpha/omega), rho = rho'
+// k_bi_xr and k_bi_p in one pass over an operator format narrower than ACC
+// (rho and beta known from k_bi_ts's dots): x += alpha p + omega s;
+// r = s - omega t;  p = r + beta (p - omega v);  partials ||r||^2.  Bound by
+// traffic: r and p are not read again, r^ is read in k_bi_ts's pass instead.
+template <int ACC, int OP>
+__global__ void __launch_bounds__(kBlk) k_bi_xrp(Fields F, BiArgs B, uint8_t* x, uint8_t* p, const uint8_t* s,
+                                                 const uint8_t* t, const uint8_t* v, uint8_t* rv, double* prr) {
+    using RA = typename AR<ACC>::R;
+    using CA = cx<RA>;
+    using CO = cx<typename AR<OP>::R>;
+    const int r = blockIdx.y;
+    const uint32_t i = blockIdx.x * kBlk + threadIdx.x;
+    double nrm = 0.0;
+    if (bi_live(B.mask, r) && i < F.vh) {
+        const double2 al = cget(B.alpha, r), om = cget(B.omega, r), be = cget(B.beta, r);
+        const RA ar = (RA)al.x, ai = (RA)al.y, wr = (RA)om.x, wi = (RA)om.y, br = (RA)be.x, bi = (RA)be.y;
+        CA xv[12], sv[12];
+        CO pv[12], tv[12], vv[12];
+        uint8_t* xrow = x + (size_t)r * F.fb_acc;
+        uint8_t* prow = p + (size_t)r * F.fb_op;
+        load_rec<ACC, 12>(xrow, F.vh, i, xv);
+        load_rec<OP, 12>(prow, F.vh, i, pv);
+        load_rec<ACC, 12>(s + (size_t)r * F.fb_acc, F.vh, i, sv);
+        load_rec<OP, 12>(t + (size_t)r * F.fb_op, F.vh, i, tv);
+        load_rec<OP, 12>(v + (size_t)r * F.fb_op, F.vh, i, vv);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const RA px = (RA)pv[k].x, py = (RA)pv[k].y, tx = (RA)tv[k].x, ty = (RA)tv[k].y;
+            xv[k].x += (ar * px - ai * py) + (wr * sv[k].x - wi * sv[k].y);
+            xv[k].y += (ar * py + ai * px) + (wr * sv[k].y + wi * sv[k].x);
+            sv[k].x -= wr * tx - wi * ty;          // sv becomes the new r
+            sv[k].y -= wr * ty + wi * tx;
+        }
+        store_rec<ACC, 12>(xrow, F.vh, i, xv);
+        store_rec<ACC, 12>(rv + (size_t)r * F.fb_acc, F.vh, i, sv);
+        nrm = norm2_12(sv);
+        CO po[12];
+#pragma unroll
+        for (int k = 0; k < 12; ++k) {
+            const RA vx = (RA)vv[k].x, vy = (RA)vv[k].y;
+            const RA dx = (RA)pv[k].x - (wr * vx - wi * vy);
+            const RA dy = (RA)pv[k].y - (wr * vy + wi * vx);
+            po[k].x = sv[k].x + (br * dx - bi * dy);
+            po[k].y = sv[k].y + (br * dy + bi * dx);
+        }
+        store_rec<OP, 12>(prow, F.vh, i, po);
+    }
+    const double t2 = group_sum(nrm);
+    if (threadIdx.x == 0) prr[(size_t)r * gridDim.x + blockIdx.x] = t2;
+}
+
+// Scalar steps, one workgroup per rhs, on nv values' partials
+// [value][nrhs][nb] (nv = 7: one array; otherwise one array per value):
+//   BI_INIT:   ||r||^2, <r^, r> -> ss, rho = <r^, r>, alpha = omega = 1
+//   BI_ALPHA:  <r^, v>          -> alpha = rho / <r^, v>
+//   BI_NALPHA: <r^, v>, ||r||^2 -> BI_NORM, then BI_ALPHA
+//   BI_OMEGA:  <t, s>, ||t||^2  -> omega = <t, s> / ||t||^2 (0 if t = 0)
+//   BI_OMBETA: <t, s>, ||t||^2, <r^, s>, <r^, t> -> BI_OMEGA, then rho' =
+//              <r^, s> - omega <r^, t> and beta as BI_BETA; what would be a
+//              breakdown there waits for ||r||^2 (flag 2), as a converged rhs
+//              has none
+//   BI_NORM:   ||r||^2          -> ss, convergence, pending breakdowns
+//   BI_BETA:   ||r||^2, <r^, r> -> ss, beta = (rho'/rho)(alpha/omega), rho = rho'
 // ||r||^2 <= tol2 ||b||^2 masks the rhs off (converged, also for b = 0); a
-// vanishing or non-finite denominator is a breakdown (flag, masked off).
-__global__ void __launch_bounds__(kRed) k_bi_scalars(int kind, BiArgs B, int nb, const double* pa,
-                                                     const double* pb, const double* pc) {
+// vanishing or non-finite denominator is a breakdown (flag 1, masked off).
+// Bound by latency: lanes for the partials there are (at most kRed), all
+// values' loads and sums side by side, the rhs's scalars loaded with them.
+struct BiParts {
+    const double* p[7];
+};
+
+template <int NV>
+__global__ void __launch_bounds__(kRed) k_bi_scalars(int kind, BiArgs B, int nb, BiParts P) {
     const int r = blockIdx.x;
-    const double a = reduce_row(pa + (size_t)r * nb, nb);
-    const double b = pb ? reduce_row(pb + (size_t)r * nb, nb) : 0.0;
-    const double c = pc ? reduce_row(pc + (size_t)r * nb, nb) : 0.0;
-    if (threadIdx.x != 0) return;
-    if (!bi_live(B.mask, r)) return;
-    auto fail = [&]() { B.flags[r] |= 1; B.mask[r] = 0; };
-    if (kind == BI_INIT) {
-        cset(B.rho, r, make_double2(b, c));
+    const bool live = bi_live(B.mask, r);
+    const int flags = B.flags[r];
+    const double2 rho = cget(B.rho, r), al = cget(B.alpha, r);
+    double2 om = cget(B.omega, r);
+    const double stop = B.tol2 * B.bb[r];
+    double acc[NV] = {}, v[NV];
+    for (int b = threadIdx.x; b < nb; b += blockDim.x)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) acc[q] += P.p[q][(size_t)r * nb + b];
+    group_sums<NV>(acc, v);
+    if (threadIdx.x != 0 || !live) return;
+    auto fail = [&]() { B.flags[r] = 1; B.mask[r] = 0; };
+    // beta from rho' = rn; false on a breakdown
+    auto set_beta = [&](double2 rn) {
+        if (!isfinite(rn.x) || !isfinite(rn.y) || !(om.x * om.x + om.y * om.y > 0.0) ||
+            !(rho.x * rho.x + rho.y * rho.y > 0.0))
+            return false;
+        cset(B.beta, r, cmul(cdiv(rn, rho), cdiv(al, om)));
+        cset(B.rho, r, rn);
+        return true;
+    };
+    // false when nothing more is to be done for this rhs
+    auto norm = [&](double a) {
+        B.ss[r] = a;
+        if (isfinite(a) && a <= stop) {      // converged (or exact)
+            if (flags & 2) B.flags[r] = flags & 1;
+            B.mask[r] = 0;
+            return false;
+        }
+        if (!isfinite(a) || (flags & 2)) { fail(); return false; }
+        return true;
+    };
+    auto alpha = [&](double2 d) {
+        if (!(d.x * d.x + d.y * d.y > 0.0) || !isfinite(d.x) || !isfinite(d.y)) fail();
+        else cset(B.alpha, r, cdiv(rho, d));
+    };
+    // false on a breakdown
+    auto omega = [&](double a, double b, double c) {
+        if (!isfinite(a) || !isfinite(b) || !isfinite(c)) { fail(); return false; }
+        om = c > 0.0 ? make_double2(a / c, b / c) : make_double2(0.0, 0.0);
+        cset(B.omega, r, om);
+        return true;
+    };
+    if constexpr (NV == 1) {
+        norm(v[0]);                                      // BI_NORM
+    } else if constexpr (NV == 2) {
+        alpha(make_double2(v[0], v[1]));                 // BI_ALPHA
+    } else if constexpr (NV == 7) {                      // BI_OMBETA
+        if (!omega(v[0], v[1], v[2])) return;
+        const double2 wt = cmul(om, make_double2(v[5], v[6]));
+        if (!set_beta(make_double2(v[3] - wt.x, v[4] - wt.y))) {
+            cset(B.beta, r, make_double2(0.0, 0.0));
+            B.flags[r] = flags | 2;
+        }
+    } else if (kind == BI_INIT) {
+        cset(B.rho, r, make_double2(v[1], v[2]));
         cset(B.alpha, r, make_double2(1.0, 0.0));
         cset(B.omega, r, make_double2(1.0, 0.0));
         cset(B.beta, r, make_double2(0.0, 0.0));
-        B.ss[r] = a;
-        if (!isfinite(a)) fail();
-        else if (a <= B.tol2 * B.bb[r]) B.mask[r] = 0;      // includes b = 0
-    } else if (kind == BI_ALPHA) {
-        const double2 d = make_double2(a, b);
-        if (!(d.x * d.x + d.y * d.y > 0.0) || !isfinite(d.x) || !isfinite(d.y)) { fail(); return; }
-        cset(B.alpha, r, cdiv(cget(B.rho, r), d));
+        norm(v[0]);
+    } else if (kind == BI_NALPHA) {
+        if (norm(v[2])) alpha(make_double2(v[0], v[1]));
     } else if (kind == BI_OMEGA) {
-        if (!isfinite(a) || !isfinite(b) || !isfinite(c)) { fail(); return; }
-        cset(B.omega, r, c > 0.0 ? make_double2(a / c, b / c) : make_double2(0.0, 0.0));
-    } else {
-        B.ss[r] = a;
-        if (isfinite(a) && a <= B.tol2 * B.bb[r]) {      // converged (or exact)
-            cset(B.beta, r, make_double2(0.0, 0.0));
-            B.mask[r] = 0;
-            return;
-        }
-        const double2 rn = make_double2(b, c), rho = cget(B.rho, r), om = cget(B.omega, r);
-        if (!isfinite(a) || !isfinite(b) || !isfinite(c) || !(om.x * om.x + om.y * om.y > 0.0) ||
-            !(rho.x * rho.x + rho.y * rho.y > 0.0)) {
-            fail();
-            return;
-        }
-        cset(B.beta, r, cmul(cdiv(rn, rho), cdiv(cget(B.alpha, r), om)));
-        cset(B.rho, r, rn);
+        omega(v[0], v[1], v[2]);
+    } else {                                             // BI_BETA
+        if (!norm(v[0])) cset(B.beta, r, make_double2(0.0, 0.0));
+        else if (!set_beta(make_double2(v[1], v[2]))) fail();
     }
 }
 
@@ -775,6 +874,15 @@ static BiArgs bi_args(const BiScalHost& h) {
     else if (ACCP == P_F32 && OPP == P_F16) { constexpr int A_ = P_F32, O_ = P_F16; CALL; }   \
     else if (ACCP == P_F32 && OPP == P_BF16) { constexpr int A_ = P_F32, O_ = P_BF16; CALL; } \
     else return hipErrorInvalidValue;
+// the operator in the vectors' own format, and in a narrower one
+#define WEO_BI_SAME(ACCP, OPP, CALL)                                                          \
+    if (ACCP == P_F64 && OPP == P_F64) { constexpr int A_ = P_F64; CALL; }                    \
+    else if (ACCP == P_F32 && OPP == P_F32) { constexpr int A_ = P_F32; CALL; }               \
+    else return hipErrorInvalidValue;
+#define WEO_BI_NARROW(ACCP, OPP, CALL)                                                        \
+    if (ACCP == P_F32 && OPP == P_F16) { constexpr int O_ = P_F16; CALL; }                    \
+    else if (ACCP == P_F32 && OPP == P_BF16) { constexpr int O_ = P_BF16; CALL; }             \
+    else return hipErrorInvalidValue;
 
 template <int PA>
 static hipError_t bi_cdot_b(int pb, const Fields& F, dim3 grid, const int* mask, const uint8_t* A,
@@ -796,7 +904,7 @@ hipError_t launch_bi_cdot(const Geom& g, int fmt_a, int fmt_b, int nrhs, const i
 }
 
 hipError_t launch_bi_s(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const BiScalHost& h, const void* r,
-                       const void* v, void* s, void* s_op, double* partial, hipStream_t st) {
+                       const void* v, void* s, void* s_op, hipStream_t st) {
     const Fields F = fields(g, fmt_acc, fmt_op);
     const dim3 grid(blas_blocks(g), nrhs), block(kBlk);
     const BiArgs B = bi_args(h);
@@ -806,8 +914,8 @@ hipError_t launch_bi_s(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const B
     auto* SO = static_cast<uint8_t*>(s_op);
     const bool sop = sp_of(fmt_acc) != sp_of(fmt_op);
     WEO_BI_PAIRS(sp_of(fmt_acc), sp_of(fmt_op),
-                 if (sop) hipLaunchKernelGGL((k_bi_s<A_, O_, true>), grid, block, 0, st, F, B, R, V, S, SO, partial);
-                 else hipLaunchKernelGGL((k_bi_s<A_, O_, false>), grid, block, 0, st, F, B, R, V, S, SO, partial))
+                 if (sop) hipLaunchKernelGGL((k_bi_s<A_, O_, true>), grid, block, 0, st, F, B, R, V, S, SO);
+                 else hipLaunchKernelGGL((k_bi_s<A_, O_, false>), grid, block, 0, st, F, B, R, V, S, SO))
     return hipGetLastError();
 }
 
@@ -824,13 +932,35 @@ hipError_t launch_bi_init(const Geom& g, int fmt_acc, int fmt_op, int nrhs, cons
 }
 
 hipError_t launch_bi_ts(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const int* mask, const void* t,
-                        const void* s, double* pre, double* pim, double* ptt, hipStream_t st) {
+                        const void* s, const void* rh, double* part, hipStream_t st) {
     const Fields F = fields(g, fmt_acc, fmt_op);
     const dim3 grid(blas_blocks(g), nrhs), block(kBlk);
     auto* T = static_cast<const uint8_t*>(t);
     auto* S = static_cast<const uint8_t*>(s);
-    WEO_BI_PAIRS(sp_of(fmt_acc), sp_of(fmt_op),
-                 hipLaunchKernelGGL((k_bi_ts<A_, O_>), grid, block, 0, st, F, mask, T, S, pre, pim, ptt))
+    auto* RH = static_cast<const uint8_t*>(rh);
+    if (rh) {
+        WEO_BI_NARROW(sp_of(fmt_acc), sp_of(fmt_op),
+                      hipLaunchKernelGGL((k_bi_ts<P_F32, O_, true>), grid, block, 0, st, F, mask, T, S, RH, part))
+    } else {
+        WEO_BI_SAME(sp_of(fmt_acc), sp_of(fmt_op),
+                    hipLaunchKernelGGL((k_bi_ts<A_, A_, false>), grid, block, 0, st, F, mask, T, S, RH, part))
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_bi_xrp(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const BiScalHost& h, void* x, void* p,
+                         const void* s, const void* t, const void* v, void* r, double* prr, hipStream_t st) {
+    const Fields F = fields(g, fmt_acc, fmt_op);
+    const dim3 grid(blas_blocks(g), nrhs), block(kBlk);
+    const BiArgs B = bi_args(h);
+    auto* X = static_cast<uint8_t*>(x);
+    auto* Pp = static_cast<uint8_t*>(p);
+    auto* S = static_cast<const uint8_t*>(s);
+    auto* T = static_cast<const uint8_t*>(t);
+    auto* V = static_cast<const uint8_t*>(v);
+    auto* R = static_cast<uint8_t*>(r);
+    WEO_BI_NARROW(sp_of(fmt_acc), sp_of(fmt_op),
+                  hipLaunchKernelGGL((k_bi_xrp<P_F32, O_>), grid, block, 0, st, F, B, X, Pp, S, T, V, R, prr))
     return hipGetLastError();
 }
 
@@ -846,8 +976,8 @@ hipError_t launch_bi_xr(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const 
     auto* T = static_cast<const uint8_t*>(t);
     auto* R = static_cast<uint8_t*>(r);
     auto* RH = static_cast<const uint8_t*>(rh);
-    WEO_BI_PAIRS(sp_of(fmt_acc), sp_of(fmt_op),
-                 hipLaunchKernelGGL((k_bi_xr<A_, O_>), grid, block, 0, st, F, B, X, Pp, S, T, R, RH, prr, pre, pim))
+    WEO_BI_SAME(sp_of(fmt_acc), sp_of(fmt_op),
+                hipLaunchKernelGGL((k_bi_xr<A_, A_>), grid, block, 0, st, F, B, X, Pp, S, T, R, RH, prr, pre, pim))
     return hipGetLastError();
 }
 
@@ -859,15 +989,28 @@ hipError_t launch_bi_p(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const B
     auto* R = static_cast<const uint8_t*>(r);
     auto* Pp = static_cast<uint8_t*>(p);
     auto* V = static_cast<const uint8_t*>(v);
-    WEO_BI_PAIRS(sp_of(fmt_acc), sp_of(fmt_op),
-                 hipLaunchKernelGGL((k_bi_p<A_, O_>), grid, block, 0, st, F, B, R, Pp, V))
+    WEO_BI_SAME(sp_of(fmt_acc), sp_of(fmt_op),
+                hipLaunchKernelGGL((k_bi_p<A_, A_>), grid, block, 0, st, F, B, R, Pp, V))
     return hipGetLastError();
 }
 #undef WEO_BI_PAIRS
+#undef WEO_BI_SAME
+#undef WEO_BI_NARROW
 
 hipError_t launch_bi_scalars(int kind, const BiScalHost& h, int nb, const double* pa, const double* pb,
                              const double* pc, hipStream_t st) {
-    hipLaunchKernelGGL(k_bi_scalars, dim3(h.nrhs), dim3(kRed), 0, st, kind, bi_args(h), nb, pa, pb, pc);
+    BiParts P = {{pa, pb, pc, nullptr, nullptr, nullptr, nullptr}};
+    if (kind == BI_OMBETA)
+        for (int q = 0; q < 7; ++q) P.p[q] = pa + (size_t)q * h.nrhs * nb;
+    const int lanes = nb < kRed ? (nb + 63) / 64 * 64 : kRed;
+    const dim3 grid(h.nrhs), block(lanes);
+    const BiArgs B = bi_args(h);
+    switch (kind) {
+        case BI_NORM: hipLaunchKernelGGL((k_bi_scalars<1>), grid, block, 0, st, kind, B, nb, P); break;
+        case BI_ALPHA: hipLaunchKernelGGL((k_bi_scalars<2>), grid, block, 0, st, kind, B, nb, P); break;
+        case BI_OMBETA: hipLaunchKernelGGL((k_bi_scalars<7>), grid, block, 0, st, kind, B, nb, P); break;
+        default: hipLaunchKernelGGL((k_bi_scalars<3>), grid, block, 0, st, kind, B, nb, P);
+    }
     return hipGetLastError();
 }
 

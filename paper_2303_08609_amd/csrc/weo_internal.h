@@ -155,7 +155,7 @@ hipError_t launch_scalars(int kind, const ScalarArgsHost& a, hipStream_t s);
 // Complex per-rhs scalars are (re, im) pairs of doubles in device memory.
 // x, r, s in fmt_acc; r^, p, v, t, s_op in fmt_op (s_op written only when
 // the two formats store spinors differently).  Partials are [nrhs][blas_blocks].
-enum { BI_INIT = 0, BI_ALPHA = 1, BI_OMEGA = 2, BI_BETA = 3 };
+enum { BI_INIT, BI_ALPHA, BI_OMEGA, BI_BETA, BI_NALPHA, BI_OMBETA, BI_NORM };
 struct BiScalHost {
     int nrhs;
     double* rho;
@@ -174,12 +174,17 @@ hipError_t launch_bi_cdot(const Geom& g, int fmt_a, int fmt_b, int nrhs, const i
 // r^ = p = r (in fmt_op), partials ||r||^2 and <r^, r> (one pass)
 hipError_t launch_bi_init(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const int* mask, const void* r,
                           void* rh, void* p, double* prr, double* pre, double* pim, hipStream_t st);
-// s = r - alpha v, s_op = s, partial ||s||^2
+// s = r - alpha v, s_op = s
 hipError_t launch_bi_s(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const BiScalHost& h, const void* r,
-                       const void* v, void* s, void* s_op, double* partial, hipStream_t st);
-// partials of <t, s> and ||t||^2
+                       const void* v, void* s, void* s_op, hipStream_t st);
+// partials [value][nrhs][blocks] of <t, s> (re, im), ||t||^2; with rh also
+// <rh, s>, <rh, t> (an operator format narrower than fmt_acc)
 hipError_t launch_bi_ts(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const int* mask, const void* t,
-                        const void* s, double* pre, double* pim, double* ptt, hipStream_t st);
+                        const void* s, const void* rh, double* part, hipStream_t st);
+// x += alpha p + omega s, r = s - omega t, p = r + beta (p - omega v), partials
+// ||r||^2 (an operator format narrower than fmt_acc)
+hipError_t launch_bi_xrp(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const BiScalHost& h, void* x, void* p,
+                         const void* s, const void* t, const void* v, void* r, double* prr, hipStream_t st);
 // x += alpha p + omega s, r = s - omega t, partials ||r||^2 and <r^, r>
 hipError_t launch_bi_xr(const Geom& g, int fmt_acc, int fmt_op, int nrhs, const BiScalHost& h, void* x,
                         const void* p, const void* s, const void* t, void* r, const void* rh, double* prr,
