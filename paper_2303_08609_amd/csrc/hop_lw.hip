@@ -26,8 +26,13 @@ namespace weo {
 // and 32^3x64 5.45 -> 1.85 ms (against one lane per site and rhs, which
 // reads links and blocks once per rhs); BF16/12 32^3x64 1.12 -> 0.96 ms,
 // FP64/12 5 rhs 20x12x28x36 240 -> 200 us (against links staged raw).
-template <class C, bool CLV> struct LwLds {
-    C lk[8][9][64];
+// FP32 12-real links stay 6 elements in LDS, rebuilt and given their phase at
+// use: complete ones (36.9 KB) leave too few workgroups on a CU (12 rhs of
+// 22x14x18x20, an apply: 99.8 us complete, 97.6 us so; the clover form,
+// bound by instructions, 363 complete, 470 so for 2 rhs of 24x18x38x74).
+template <int SP, bool L12, bool CLV> constexpr int lw_elems() { return SP == P_F32 && L12 && !CLV ? 6 : 9; }
+template <class C, bool CLV, int NE> struct LwLds {
+    C lk[8][NE][64];
     C cb[CLV ? 2 : 1][CLV ? kCloverSlots : 1][CLV ? 64 : 1];
 };
 
@@ -55,9 +60,9 @@ __device__ __forceinline__ LinkAt link_at(const HopParams& P, const Nbr& nb, uin
 // Links t = wv, wv + W, ... of the site to LDS (W >= 2, so at most 4): the
 // loads of NB of them are issued before the first is used (FP64: 2; 4 of its
 // links would not fit next to the first record).
-template <int SP, int LP, bool L12, class C>
+template <int SP, int LP, bool L12, int NE, class C>
 __device__ __forceinline__ void lw_stage_links(const HopParams& P, const Nbr& nb, uint32_t ih, uint32_t lane, int wv,
-                                               int W, C (&lk)[8][9][64]) {
+                                               int W, C (&lk)[8][NE][64]) {
     using R = decltype(C().x);
     constexpr int NB = SP == P_F64 ? 2 : 4;
     RawRec<LP, L12 ? 6 : 9, true> raw[NB];
@@ -82,12 +87,17 @@ __device__ __forceinline__ void lw_stage_links(const HopParams& P, const Nbr& nb
                 C u[9];
 #pragma unroll
                 for (int e = 0; e < (L12 ? 6 : 9); ++e) { u[e].x = (R)w[e].x; u[e].y = (R)w[e].y; }
-                if constexpr (L12) complete_link(u);
-                // ph U for both hops: the backward one multiplies by (ph U)^dag
-                const int mu = t >> 1;
-                const C ph = edge[j] ? mk<C>((R)P.ph[mu][0], (R)P.ph[mu][1]) : mk<C>(R(1), R(0));
+                if constexpr (NE == 6) {
 #pragma unroll
-                for (int e = 0; e < 9; ++e) lk[t][e][lane] = mul(ph, u[e]);
+                    for (int e = 0; e < 6; ++e) lk[t][e][lane] = u[e];
+                } else {
+                    if constexpr (L12) complete_link(u);
+                    // ph U for both hops: the backward one multiplies by (ph U)^dag
+                    const int mu = t >> 1;
+                    const C ph = edge[j] ? mk<C>((R)P.ph[mu][0], (R)P.ph[mu][1]) : mk<C>(R(1), R(0));
+#pragma unroll
+                    for (int e = 0; e < 9; ++e) lk[t][e][lane] = mul(ph, u[e]);
+                }
             }
         }
     }
@@ -109,10 +119,10 @@ template <int SP, bool DOT> constexpr int lw_waves() { return SP == P_F64 ? 2 : 
 // Two record slots: the neighbour record of direction K + 1 is fetched while
 // direction K is computed; the last direction of one right-hand side fetches
 // the first record of the next.
-template <int SP, bool DAG, int K, class C>
-__device__ __forceinline__ void lw_step(const HopParams& P, const C (&lk)[8][9][64], uint32_t lane,
+template <int SP, bool DAG, int K, int NE, class C>
+__device__ __forceinline__ void lw_step(const HopParams& P, const C (&lk)[8][NE][64], uint32_t lane,
                                         const uint8_t* in, const uint8_t* in_next, const NbrOff& no,
-                                        RawRec<SP, 12> (&ring)[2], C* acc) {
+                                        RawRec<SP, 12> (&ring)[2], uint32_t edges, C* acc) {
     constexpr int MU = K / 2;
     constexpr int SF = DAG ? -1 : 1;
     load_spinor<SP>(K + 1 < 8 ? in : in_next, P.g.vh, no.o[(K + 1) & 7], ring[(K + 1) & 1]);
@@ -122,17 +132,25 @@ __device__ __forceinline__ void lw_step(const HopParams& P, const C (&lk)[8][9][
     C h[6], u[9];
     project_raw<SP, MU, S>(ring[K & 1], h);
 #pragma unroll
-    for (int e = 0; e < 9; ++e) u[e] = lk[K][e][lane];
+    for (int e = 0; e < NE; ++e) u[e] = lk[K][e][lane];
+    if constexpr (NE == 6) {
+        using R = decltype(C().x);
+        complete_link(u);
+        const C ph = edges >> K & 1u ? mk<C>((R)P.ph[MU][0], (R)(FWD ? P.ph[MU][1] : -P.ph[MU][1])) : mk<C>(R(1), R(0));
+#pragma unroll
+        for (int e = 0; e < 6; ++e) h[e] = mul(ph, h[e]);
+    }
     hop_half<MU, S, FWD, PH_REAL, false>(h, u, false, C{}, acc);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (K + 1 < 8) lw_step<SP, DAG, K + 1>(P, lk, lane, in, in_next, no, ring, acc);
+    if constexpr (K + 1 < 8) lw_step<SP, DAG, K + 1>(P, lk, lane, in, in_next, no, ring, edges, acc);
 }
 
 template <int SP, int LP, bool L12, bool DAG, bool DOT, bool CLV>
 __global__ void __launch_bounds__(64 * lw_maxw<SP>(), (lw_waves<SP, DOT>())) k_hop_lw(const MrhsParams M) {
     using R = typename Arith<SP>::R;
     using C = cx<R>;
-    __shared__ LwLds<C, CLV> lds;
+    constexpr int NE = lw_elems<SP, L12, CLV>();
+    __shared__ LwLds<C, CLV, NE> lds;
     const HopParams& P = M.h;
     const uint32_t n = P.g.vh;
     const uint32_t nchunk = (n + 63) >> 6;
@@ -147,7 +165,13 @@ __global__ void __launch_bounds__(64 * lw_maxw<SP>(), (lw_waves<SP, DOT>())) k_h
     const uint32_t ih = sp.base + lane;
     const bool valid = ih < sp.end;
     Nbr nb;
-    if (valid) nb = neighbours(P.g, decode(P.g, ih, P.out_par));
+    uint32_t edges = 0;
+    if (valid) {
+        nb = neighbours(P.g, decode(P.g, ih, P.out_par));
+        if constexpr (NE == 6)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) edges |= (uint32_t)nb.edge[k] << k;
+    }
     // the first record is on its way while the links are staged
     RawRec<SP, 12> ring[2];
     NbrOff no;
@@ -177,7 +201,7 @@ __global__ void __launch_bounds__(64 * lw_maxw<SP>(), (lw_waves<SP, DOT>())) k_h
             C acc[12];
 #pragma unroll
             for (int k = 0; k < 12; ++k) acc[k] = czero<C>();
-            lw_step<SP, DAG, 0>(P, lds.lk, lo, in, in_next, no, ring, acc);
+            lw_step<SP, DAG, 0>(P, lds.lk, lo, in, in_next, no, ring, edges, acc);
             if constexpr (CLV) {
                 const BlockInLds<C> b0{lds.cb[0], lo}, b1{lds.cb[1], lo};
                 clover_apply_blocks(b0, b1, acc);
