@@ -723,7 +723,7 @@ bool tuning_verbose() {
 // An entry is used only if its shape is among the current candidates for
 // that key (so a stale or edited file can pick a slower shape, never an
 // invalid launch).  New results are appended, one line per write.
-constexpr int kTuneCacheVersion = 5;
+constexpr int kTuneCacheVersion = 6;
 
 const char* tune_cache_path() {
     const char* p = getenv("WILSON_EO_TUNE_CACHE");
@@ -810,6 +810,27 @@ hipError_t time_cfg(const HopLaunch& h, const MrhsCfg& c, hipStream_t s, hipEven
     return hipSuccess;
 }
 
+// Packed FP16 arithmetic rounds the projected half spinor, so it is taken
+// only where it pays by itself: the packed form with LDS-staged links stays a
+// choice where the packed form with links in registers beats every
+// FP32-arithmetic form with links in registers (FP16/12 hop of 12 fields,
+// packed and FP32: 16^3x32 25.6 against 33.2 us, it stays; 16^4 24.2 against
+// 18.0, it goes, though the LDS forms take 13.3 packed and 15.2 in FP32).
+void drop_packed_lds(std::vector<std::pair<float, MrhsCfg>>& timed) {
+    float packed = 1e30f, fp32 = 1e30f;
+    for (const auto& t : timed) {
+        const int nr = t.second.nr;
+        if (nr == -2 || nr == -4) packed = std::min(packed, t.first);
+        else if (nr > kNrLw) fp32 = std::min(fp32, t.first);
+    }
+    if (packed < fp32) return;
+    timed.erase(std::remove_if(timed.begin(), timed.end(),
+                               [](const std::pair<float, MrhsCfg>& t) {
+                                   return t.second.nr == kNrLw16 || t.second.nr == kNrLw16Deep;
+                               }),
+                timed.end());
+}
+
 // Every candidate timed briefly (3 launches), then the 4 fastest again over
 // 12 launches each: single short timings vary by several per cent between
 // neighbouring shapes, which had made the choice drift from run to run.
@@ -830,6 +851,7 @@ hipError_t tune(const HopLaunch& h, hipStream_t s, TuneEntry* best) {
         timed.push_back({us, c});
     }
     if (err == hipSuccess) {
+        drop_packed_lds(timed);
         std::sort(timed.begin(), timed.end(), [](const std::pair<float, MrhsCfg>& a,
                                                  const std::pair<float, MrhsCfg>& b) { return a.first < b.first; });
         const size_t nfinal = timed.size() < 4 ? timed.size() : 4;
