@@ -139,7 +139,8 @@ int weo_set_mrhs_shape(int nr, int sites, int persist, int bz, int split);
  * query the length.  A multi-rhs launch is tuned on its first call by
  * timing every candidate shape on the caller's stream and buffers, except
  * an in-place axpy (y is out) and a launch on a stream under capture, which
- * run untuned.  With the environment
+ * run untuned.  The hops of wilson_eo_clover_hop and wilson_eo_clover_apply
+ * take their shape from a rule: those calls never wait for the stream.  With the environment
  * variable WILSON_EO_TUNE_CACHE naming a file, tuned shapes are appended to
  * it (a header line with the cache version and GPU architecture, then one
  * text line per key) and read back by later processes, which then skip the

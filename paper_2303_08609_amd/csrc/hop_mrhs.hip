@@ -18,7 +18,8 @@
 // The launch shape (NR, sites per workgroup, persistence) is picked per
 // (lattice, format, nrhs) by timing every candidate on the first call with
 // that key on the caller's stream and buffers (one stream synchronisation),
-// then cached for the life of the process.  The candidates also cover the
+// then cached for the life of the process; the hops of the clover operator
+// take theirs from a rule instead and never wait.  The candidates also cover the
 // workgroup schedule (z-strips of 2, 4 or 8 planes, make_sched), which keeps
 // the +-t neighbours of 12 fields inside L2.  WEO_TUNE=0 in the environment
 // disables the search and uses NR = 3, 64 sites, no persistence;
@@ -653,15 +654,15 @@ std::vector<MrhsCfg> candidates(const HopLaunch& h) {
     std::vector<MrhsCfg> v;
     v.push_back({1, 0, 0, 0, 0});
     const bool wide = fmt_info(h.fmt).spinor_prec == P_F64;
-    // the fused dot and the clover blocks: single-rhs and LDS-staged kernels only
-    const bool dot = h.dmode != 0 || h.clv != nullptr;
+    // the fused dot: single-rhs and LDS-staged kernels only
+    const bool dot = h.dmode != 0;
     if (lr_supported(h.fmt) && !dot)
         for (int s : {64, 128, 256})
             for (int persist : {0, 1})
                 for (int bz : {0, 2, 4, 8}) {
                     if (bz && make_sched(h.g, bz, (uint32_t)s, h.partial != nullptr).bz != bz) continue;
                     for (int nr : {-1, -3}) v.push_back({nr, s, persist, bz, 0});
-                    if (lr16_supported(h.fmt) && !h.fp32)
+                    if (lr16_supported(h.fmt))
                         for (int nr : {-2, -4}) v.push_back({nr, s, persist, bz, 0});
                 }
     int w0 = 0;
@@ -674,7 +675,7 @@ std::vector<MrhsCfg> candidates(const HopLaunch& h) {
             for (int f : {0, 6}) {                // right-hand sides per sweep (0: all)
                 if (f && (f >= h.nrhs || f < w)) continue;
                 v.push_back({kNrLw, w, 0, bz, f});
-                if (lr16_supported(h.fmt) && !h.fp32 && !dot) {
+                if (lr16_supported(h.fmt) && !dot) {
                     v.push_back({kNrLw16, w, 0, bz, f});
                     v.push_back({kNrLw16Deep, w, 0, bz, f});
                 }
@@ -908,6 +909,56 @@ int set_mrhs_shape(int nr, int sites, int persist, int bz, int split) {
     return 0;
 }
 
+// Shape of the clover operator's hops (h.clv, or the plain hop that ends its
+// adjoint), picked without timing so that the call stays asynchronous.  Links
+// and blocks staged in LDS are read once for all fields, but a workgroup walks
+// them one after the other; one lane per site and field has them side by side
+// and wins while its workgroups fit the chip at once (2^16 lanes, 2^14 for
+// the small-lattice kernel in FP64) unless the fields are few, and for 2 or 3
+// FP16 fields throughout.  Strips of 4 z-planes pay where a field's t slices
+// outgrow L2.  Clover hop with the axpy, one lane per site and field, then
+// LDS with the wavefronts below (us; 2 / 3 / 4 / 6 / 12 fields; * not taken):
+//   FP64/18  4096 sites  7.3, 10.2* / 7.5, 10.9* / 7.7, 11.9* / 13.3, 14.8* / 17.4, 25.5*
+//           13824        14.2, 12.6 / 19.2, 13.9 / 22.6, 15.7 / 37.1, 19.8 / 59.2, 32.4
+//           65536        49.2, 48.9* / 74.8, 53.6 / 96.7, 61.1 / 143, 81.6 / 275, 139
+//         1048576        991, 835 / 1528, 888 / 2057, 1022 / 3106, 1377 / 6239, 2355
+//   FP32/18 13824        5.6, 7.7* / 10.7, 8.2 / 12.1, 8.3 / 19.5, 9.4 / 31.0, 14.9
+//           65536        24.2, 22.0 / 34.6, 24.2 / 45.3, 26.6 / 66.4, 34.3 / 123, 57.8
+//         1048576        463, 333 / 700, 386 / 945, 432 / 1425, 597 / 2905, 1009
+//   FP16/12 20736        6.4, 9.8* / 7.2, 9.6* / 10.2, 9.3 / 11.7, 12.0 / 20.5, 16.5
+//           65536        10.7, 18.4* / 14.5, 19.0* / 17.5, 19.2 / 25.6, 25.7 / 49.2, 32.2
+//         1048576        185, 290* / 264, 291* / 357, 304 / 535, 383 / 1105, 581
+// Over 490 such cases (all formats, 2 to 16 fields, 4096 to 1048576 sites) the
+// rule is 0.5 % slower than the fastest shape on average; the adjoint's plain
+// hop, where registers may hold the links too, 1.3 %.
+static MrhsCfg clover_shape(const HopLaunch& h) {
+    const uint32_t vh = h.g.vh;
+    const int n = h.nrhs, prec = fmt_info(h.fmt).spinor_prec;
+    const bool wide = prec == P_F64, half = prec == P_F16 || prec == P_BF16, plain = !h.clv;
+    const uint64_t work = (uint64_t)vh * (uint64_t)n;
+    const MrhsCfg single = {1, 0, 0, 0, 0};
+    if (plain && half && n <= 3) return vh > (1u << 15) ? MrhsCfg{n, 64, 0, 0, 0} : single;
+    if (plain && wide && n == 2 && vh > (1u << 14) && vh <= (1u << 17)) return {2, 64, 0, 0, 0};
+    bool lds;
+    if (half) lds = vh > (1u << 13) && work > (1u << 16) &&
+                    (n >= 4 || (n == 3 && vh > (1u << 19) && !fmt_info(h.fmt).link12));
+    else if (wide) lds = (work > (1u << 16) && (n >= 3 || vh > (1u << 17))) ||
+                         (n <= 5 && vh <= (1u << 14) && work > (1u << 14));
+    else lds = work > (1u << 16) || (n <= 6 && work > (1u << 15));
+    if (!lds) return single;
+    if (plain && !half && !wide && vh > (1u << 15) && vh <= (1u << 17)) return {-1, 256, 0, 0, 0};
+    // wavefronts: one per field while the lattice is small, then an even share
+    // of the fields, fewer where LDS already holds a CU to one workgroup
+    const int few = n <= 4 ? n : n <= 6 ? 6 : n <= 8 ? 8 : 12, third = n <= 4 ? n : n <= 6 ? 3 : 4;
+    int w;
+    if (plain && wide && vh > (1u << 14)) w = third;
+    else if (plain && vh > (1u << 15)) w = half ? 4 : 2;
+    else if (wide) w = n <= 6 ? few : 4;
+    else if (vh <= (1u << 14)) w = few;
+    else w = !half ? third : n <= 8 ? few : 8;
+    return {kNrLw, w, 0, vh > (1u << 17) ? 4 : 0, 0};
+}
+
 // The shape where nothing can be timed: links staged in LDS for as many
 // wavefronts as right-hand sides, up to 6.
 static MrhsCfg untuned_shape(const HopLaunch& h) { return {kNrLw, h.nrhs < 5 ? h.nrhs : 6, 0, 0, 0}; }
@@ -943,8 +994,9 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
         if (c.nr > h.nrhs) c.nr = h.nrhs;
         return c.nr <= 1 ? launch_hop_single(h, s) : launch_hop_mrhs(h, c, s);
     }
+    if (h.clv || h.fp32) return run_cfg(h, clover_shape(h), s);
     const int epi = (h.y != nullptr ? 1 : 0) + (h.partial != nullptr ? 2 : 0) + (h.z != nullptr ? 4 : 0) +
-                    (h.dmode != 0 ? 8 : 0) + (h.clv ? 16 : 0) + (h.fp32 ? 32 : 0);
+                    (h.dmode != 0 ? 8 : 0);
     const TuneKey key{h.g.lx, h.g.ly, h.g.lz, h.g.lt, h.fmt, h.nrhs, epi};
     TuneEntry e;
     bool have = false;
@@ -981,7 +1033,7 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t s) {
             const hipError_t err = tune(h, s, &e);
             if (err != hipSuccess) return err;
         } else {
-            e.cfg = h.clv ? untuned_shape(h) : MrhsCfg{h.nrhs >= 3 ? 3 : h.nrhs, 64, 0, 0, 0};
+            e.cfg = {h.nrhs >= 3 ? 3 : h.nrhs, 64, 0, 0, 0};
             e.us = 0.f;
         }
         std::lock_guard<std::mutex> lk(g_tune_mu);
