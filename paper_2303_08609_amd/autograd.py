@@ -77,8 +77,11 @@ class WilsonApply(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g_out):
-        u, psi, u_p, *keep = ctx.saved_tensors
+        u, psi, *keep = ctx.saved_tensors
         lat, fmt, dagger = ctx.lat, ctx.fmt, ctx.dagger
+        if any(t.dtype != torch.uint8 for t in keep):
+            keep = ()       # a saved-tensor hook that converts what it is given, as it may u and psi
+        u_p = keep[0] if keep else lat.pack_gauge(u.contiguous(), fmt)
         g_p = lat.pack_spinor(g_out.contiguous(), fmt)
         g_u = g_psi = lam_o = None
         if ctx.needs_input_grad[1]:
@@ -88,7 +91,7 @@ class WilsonApply(torch.autograd.Function):
         if ctx.needs_input_grad[0]:
             if dagger:
                 raise NotImplementedError("link gradient of M^dag is not provided")
-            x_p, r_o = keep
+            x_p, r_o = keep[1:] if keep else (lat.pack_spinor(psi.contiguous(), fmt), None)
             g_u = torch.empty(lat.gauge_shape(), dtype=u.dtype, device=u.device)
             _link_grad_into(lat, fmt, u_p, g_p, x_p, -lat.kappa ** 2, g_u, False, lam_o=lam_o, r_o=r_o)
         return g_u, g_psi, None, None
