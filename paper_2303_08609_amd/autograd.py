@@ -58,10 +58,18 @@ def _link_grad_into(lat, fmt, u_packed, eta_p, psi_p, coeff, out, accumulate, pr
                               _stream()), "wilson_eo_force")
 
 
+# Packed links up to this size are kept from forward to backward.
+KEEP_LINK_BYTES = 1 << 29
+
+
 class WilsonApply(torch.autograd.Function):
-    """The packed links, and for a link gradient the packed psi and H_oe psi
-    (the odd half the apply computes on its way), are saved for backward:
-    packing them and hopping again took a quarter of a backward pass."""
+    """Backward needs the packed links, and for a link gradient the packed psi
+    and H_oe psi (the odd half the apply computes on its way).  Packing them
+    and hopping again takes a quarter of a backward pass, so they are saved
+    next to u and psi: per site 576 bytes of links and 192 of fields in FP64,
+    half that in FP32, for every apply of a graph.  Links of more than
+    KEEP_LINK_BYTES (FP64: more than 932067 sites), of which a graph of
+    some hundred applies would not fit the card, are packed again instead."""
 
     @staticmethod
     def forward(ctx, u, psi, lat: Lattice, dagger: bool = False):
@@ -70,8 +78,10 @@ class WilsonApply(torch.autograd.Function):
         x_p = lat.pack_spinor(psi.contiguous(), fmt)
         odd = lat.new_spinor(fmt)
         out_p = lat.apply(u_p, x_p, fmt, dagger=dagger, tmp=odd)
-        keep = (x_p, odd) if ctx.needs_input_grad[0] and not dagger else ()
-        ctx.save_for_backward(u, psi, u_p, *keep)
+        keep = ()
+        if u_p.numel() <= KEEP_LINK_BYTES:
+            keep = (u_p, x_p, odd) if ctx.needs_input_grad[0] and not dagger else (u_p,)
+        ctx.save_for_backward(u, psi, *keep)
         ctx.lat, ctx.fmt, ctx.dagger = lat, fmt, dagger
         return lat.unpack_spinor(out_p, fmt, dtype=psi.dtype)
 
