@@ -291,7 +291,9 @@ int wilson_eo_clover_apply(const weo_lattice* lat, const weo_format* fmt, int da
 /* The even-odd operator of Eq. (4), left-hand side, on the even sublattice:
  *   out = M in = in - kappa^2 H_eo H_oe in   (dagger = 0)
  *   out = M^dag in                           (dagger = 1)
- * tmp is caller scratch for nrhs odd-parity spinors (weo_spinor_bytes). */
+ * tmp holds nrhs odd-parity spinors (weo_spinor_bytes) and is left with
+ * H_oe in (dagger = 1: H_oe^dag in), as wilson_eo_hop writes it; link
+ * gradients take it from there. */
 int wilson_eo_apply(const weo_lattice* lat, const weo_format* fmt, int dagger,
                     const void* u, const void* in, void* out, void* tmp,
                     int nrhs, void* stream);
