@@ -231,9 +231,11 @@ __global__ void __launch_bounds__(kSapMaxSites) k_sap_sweep(const SapParams P) {
 // in lattice order in the first and last cycle only.  Only one colour's
 // blocks are launched, x neighbours on one XCD (they share cache lines of the
 // links).
-// What bounds it: vector issue (about 1300 instructions per lane and step,
-// 200 of them the FP64 block sums) at 2 wavefronts per SIMD -- 256 registers
-// and 74 KiB of LDS for 256 sites.  One sweep at 32^3x64 with 4^4 blocks and
+// What bounds it: vector issue and latency, at 2 wavefronts per SIMD (256
+// registers and 74 KB of LDS for 256 sites).  Counters at 32^3x64, 4^4 blocks:
+// about 1300 vector instructions per lane and step (200 of them the FP64 block
+// sums) issue on 58 % of the cycles, the wavefronts wait 21 % of theirs, and
+// 0.95 GB read and 0.16 written in 295 us are 3.8 TB/s.  One sweep at 32^3x64 with 4^4 blocks and
 // 4 steps: 290 us, against 1390 us for k_sap_sweep, whose 8 links per site
 // and solution cost half the occupancy and whose neighbour reads fetch whole
 // cache lines for 32 bytes.
@@ -816,8 +818,9 @@ static int sap_face_words(const SapGeom& sg, int* off) {
 
 // Whether the faces of all blocks fit two of the three scratch fields (one
 // field is 6 words per site, one colour's faces lie in each): every layout
-// with sum 1 / b_mu <= 2 over the cut directions, so all but blocks of
-// extent 1 in two or more of them.  The others take k_sap_sweep.
+// with sum 1 / b_mu <= 2 over the cut directions: 2^4 (2) and (1, 4, 4, 4)
+// (1.75) do, (1, 2, 2, 4) (2.25) and (1, 2, 2, 2) (2.5) do not.  The others
+// take k_sap_sweep.
 static bool sap_blocks_fit(const SapGeom& sg) { return sap_face_words(sg, nullptr) <= 12 * sg.bvol; }
 
 template <bool L12, bool WRAP>
