@@ -76,18 +76,25 @@ static void read_env_tuning() {
 // z strips for lattices whose t slices outgrow an XCD's 4 MiB of L2: walked in
 // lexicographic order, a slice's spinors are gone before the next slice wants
 // them.  With 8 strips each of the 8 XCDs walks one strip through all of t
-// (with 4, half of t), so the strip's three slices stay in its L2 and only the
-// strip's edge planes are read twice.  Height Lz / 8 if that is 5 planes or
-// more (lower ones lose more at the edges than they gain), otherwise Lz / 4 of
-// 6 or more, otherwise none; other numbers of strips leave XCDs in the middle
-// of two strips.  Strips measured (apply, us, none -> strips; parity slice):
+// (with 4, half of t), and three slices of a strip are an eighth (a quarter)
+// of the plane-wide ones.  Height Lz / 8 if that is 5 planes or more (lower
+// ones lose more at the edges than they gain), otherwise Lz / 4 of 6 or more,
+// otherwise none; other numbers of strips leave XCDs in the middle of two
+// strips.  Strips measured (apply us, none -> strips; parity slice):
 //   FP16/12 48^3x96 (2.6 MB) 702 -> 672, FP32/12 48^3x64 (5.3) 927 -> 896,
 //   FP32/12 40^3x48 (3.1) 413 -> 400, FP32/12 64^3x24 (12.6) 863 -> 787,
-//   FP64/18 48^3x32 (10.6) 1302 -> 1179, FP64/12 32^3x64 (3.1) 618 -> 574;
-// in smaller slices they gain nothing or cost: FP32/18 32^3x64 (1.6) 290 -> 300,
-// FP64/18 24^3x96 (1.3) 468 -> 469, FP16/12 40^3x80 (1.5) 315 -> 314; hence the
-// line at 2.5 MB.  An XCD's walk of few slices gains little: 8 slices (FP32/18
-// 128x64x40x8) 406 -> 408, 14 (FP64/18 28x44x52x28) 632 -> 637, but 12
+//   FP64/18 48^3x32 (10.6) 1302 -> 1179, FP64/12 32^3x64 (3.1) 618 -> 574.
+// Bytes fetched past L2 and time of one hop: FP16/12 48^3x96 1632 -> 1375 MB,
+// 325 -> 311 us; FP32/12 48^3x64 2077 -> 1882 MB, 433 -> 413 us; but FP64/18
+// 48^3x32 3515 -> 3434 MB, 610 -> 563 us and FP64/12 64^2x32x24 2345 -> 2386 MB,
+// 436 -> 396 us: FP64 gains time without saving bytes, for a reason the
+// counters read do not show.
+// Smaller slices: FP16/12 gains 4 to 7 % down to 1.9 MB (44^2x40x48 225 -> 210,
+// 44^2x48x64 387 -> 370) and none at 1.5 (40^3x80 315 -> 314), FP32/12 at 2.0 to
+// 2.5 MB between 2 % gained and 3 % lost (36x32x40x48 244 -> 252), FP64 at 1.8 to
+// 2.4 MB up to 8 % lost (28x20x40x64 477 -> 514), FP32/18 32^3x64 (1.6) 290 -> 300;
+// hence one line at 2.5 MB.  An XCD's walk of few slices gains little: 8 slices
+// (FP32/18 128x64x40x8) 406 -> 408, 14 (FP64/18 28x44x52x28) 632 -> 637, but 12
 // (FP64/18 64x64x32x24) 1158 -> 1059; hence 12.  The clover hop, with its block
 // reads, measured the same with and without (it keeps lexicographic order).
 int hop_strip(const Geom& g, int fmt) {

@@ -20,12 +20,16 @@ namespace weo {
 // [direction][element][site], so the 64 lanes of a read touch consecutive
 // words.  With CLV the output sites' two clover blocks are staged as well
 // and multiply the sum before the epilogue (clover_core.h).
-// What bounds it: memory traffic beyond L2 for FP32 and FP64 (the neighbour
-// records read again), vector issue for the clover form in FP16.  Apply,
-// 12 rhs: clover FP16/12 16^3x32 104 -> 74 us, FP32/18 16^3x32 253 -> 105 us
-// and 32^3x64 5.45 -> 1.85 ms (against one lane per site and rhs, which
-// reads links and blocks once per rhs); BF16/12 32^3x64 1.12 -> 0.96 ms,
-// FP64/12 5 rhs 20x12x28x36 240 -> 200 us (against links staged raw).
+// What bounds it: memory traffic beyond L2 for FP32, vector issue for the
+// clover form in FP16, latency for FP64 (12-real links, 5 rhs of 20x12x28x36:
+// vector issue on 25 % of the cycles, wavefronts waiting 48 % of theirs).  At
+// 218 registers FP64 has 2 wavefronts per SIMD where links staged raw left
+// one: twice the neighbour records in flight read more again (12 rhs, 32^3x64,
+// 6.0 -> 8.0 GB past L2) in less time (1847 -> 1762 us).  Apply, 12 rhs: clover
+// FP16/12 16^3x32 105 -> 71 us, FP32/18 16^3x32 253 -> 111 us and 32^3x64
+// 5.45 -> 1.92 ms (against one lane per site and rhs, which reads links and
+// blocks once per rhs); BF16/12 32^3x64 1.12 -> 0.96 ms, FP64/12 5 rhs
+// 20x12x28x36 240 -> 219 us (against links staged raw).
 // FP32 12-real links stay 6 elements in LDS, rebuilt and given their phase at
 // use: complete ones (36.9 KB) leave too few workgroups on a CU (12 rhs of
 // 22x14x18x20, an apply: 99.8 us complete, 97.6 us so; the clover form,
