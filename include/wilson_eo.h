@@ -137,7 +137,7 @@ int weo_set_mrhs_shape(int nr, int sites, int persist, int bz, int split);
  * truncated to len bytes), one per (lattice, format, nrhs, epilogue: 1 axpy,
  * 2 norm partials); returns the untruncated length.  buf may be NULL to
  * query the length.  A multi-rhs launch is tuned on its first call by
- * timing every candidate shape on the caller's stream and buffers, except
+ * timing candidate shapes on the caller's stream and buffers, except
  * an in-place axpy (y is out) and a launch on a stream under capture, which
  * run untuned.  The hops of wilson_eo_clover_hop and wilson_eo_clover_apply
  * take their shape from a rule: those calls never wait for the stream.  With the environment

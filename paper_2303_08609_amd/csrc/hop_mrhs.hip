@@ -16,7 +16,7 @@
 // same XCD-contiguous block order as the single-rhs kernel.
 //
 // The launch shape (NR, sites per workgroup, persistence) is picked per
-// (lattice, format, nrhs) by timing every candidate on the first call with
+// (lattice, format, nrhs) by timing candidates on the first call with
 // that key on the caller's stream and buffers (one stream synchronisation),
 // then cached for the life of the process; the hops of the clover operator
 // take theirs from a rule instead and never wait.  The candidates also cover the
@@ -832,9 +832,13 @@ void drop_packed_lds(std::vector<std::pair<float, MrhsCfg>>& timed) {
                 timed.end());
 }
 
-// Every candidate timed briefly (3 launches), then the 4 fastest again over
-// 12 launches each: single short timings vary by several per cent between
-// neighbouring shapes, which had made the choice drift from run to run.
+// Every candidate without strips timed briefly (3 launches), then the 8
+// fastest of them in strips, then the 4 fastest of all again over 12 launches
+// each: single short timings vary by several per cent between neighbouring
+// shapes, which had made the choice drift from run to run.  Strips of all
+// candidates would take 2.9 times as long (the axpy of 12 FP16/12 fields of
+// 24^3x48: 377 shapes, 305 ms, against 119, 100 ms) and found nothing more than
+// 0.7 % faster over 532 keys.
 hipError_t tune(const HopLaunch& h, hipStream_t s, TuneEntry* best) {
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return hipErrorUnknown;
@@ -842,19 +846,32 @@ hipError_t tune(const HopLaunch& h, hipStream_t s, TuneEntry* best) {
     best->us = 1e30f;
     best->cfg = {1, 0, 0, 0, 0};
     hipError_t err = hipSuccess;
-    std::vector<std::pair<float, MrhsCfg>> timed;
-    for (const MrhsCfg& c : candidates(h)) {
+    using Timed = std::pair<float, MrhsCfg>;
+    std::vector<Timed> timed;
+    const auto faster = [](const Timed& a, const Timed& b) { return a.first < b.first; };
+    const auto brief = [&](const MrhsCfg& c) {
         float us = 0.f;
-        if ((err = time_cfg(h, c, s, e0, e1, 3, &us)) != hipSuccess) break;
+        if ((err = time_cfg(h, c, s, e0, e1, 3, &us)) != hipSuccess) return;
         if (tuning_verbose())
             fprintf(stderr, "[weo tune] fmt %d nrhs %d: nr %d sites %d persist %d bz %d split %d -> %.1f us\n",
                     h.fmt, h.nrhs, c.nr, c.s, c.persist, c.bz, c.split, us);
         timed.push_back({us, c});
-    }
+    };
+    const std::vector<MrhsCfg> all = candidates(h);
+    for (const MrhsCfg& c : all)
+        if (c.bz == 0 && err == hipSuccess) brief(c);
     if (err == hipSuccess) {
         drop_packed_lds(timed);
-        std::sort(timed.begin(), timed.end(), [](const std::pair<float, MrhsCfg>& a,
-                                                 const std::pair<float, MrhsCfg>& b) { return a.first < b.first; });
+        std::sort(timed.begin(), timed.end(), faster);
+        const std::vector<Timed> lead(timed.begin(), timed.begin() + (timed.size() < 8 ? timed.size() : 8));
+        for (const MrhsCfg& c : all)
+            for (const Timed& l : lead)
+                if (c.bz != 0 && c.nr == l.second.nr && c.s == l.second.s && c.persist == l.second.persist &&
+                    c.split == l.second.split && err == hipSuccess)
+                    brief(c);
+    }
+    if (err == hipSuccess) {
+        std::sort(timed.begin(), timed.end(), faster);
         const size_t nfinal = timed.size() < 4 ? timed.size() : 4;
         for (size_t k = 0; k < nfinal; ++k) {
             float us = 0.f;
